@@ -59,7 +59,7 @@ def persistent_applies(specs, compress: str, parties: int, implicit: bool) -> bo
 
 
 def stage_work(stage: str, specs, mode: str, f: int = 0, kbits: int = 64, compress: str = "n",
-               implicit: bool = False, parties: int = 2):
+               implicit: bool = False, parties: int = 2, rns: bool = False):
     """Algorithmic work of one launch of a kernel stage over the layer batch:
     ("hbm", bytes) or ("mfma", int8 ops), for the fused step
     (online phase + verification).  16 B per Z_2^128 element; per element,
@@ -96,7 +96,19 @@ def stage_work(stage: str, specs, mode: str, f: int = 0, kbits: int = 64, compre
     and writes 32 B per K x N entry, and conv_compress reads U, tB_p:
     16 n + 16 B per input element.
     With k = s = 32 elements are 8 B (every byte figure halves) and a ring
-    MAC is 36 digit products."""
+    MAC is 36 digit products.
+    rns: every matrix-core layer's products go through residues (36 residue
+    planes of 1 B per element; two-party layers neither implicit convolutions
+    nor compressed along M open E and U in rns_open):
+      rns_open   K x N: as open_u, and the planes of [B]_p, U (SPDZ2k also
+                 [tB]_p); M x K: reads X_p, A_p (SPDZ2k also tA_p), writes E
+                 and the planes of E, A_0 + E, [A]_1 (SPDZ2k also the folded
+                 tag operands): 144 + 36 ops and 80 + 36 ops (+ 32) B
+      row_pass   of those layers, M x K: reads E, tX_p, tA_p: 80 B
+      rns_pack   the other layers' operands: 16 B read, 36 B written
+      rns_gemm   2 * 36 int8 ops per ring MAC
+      rns_fold   M x N per product: 36 B of residues and the constant term
+                 read, the product written: 68 B"""
     scale = 1 if kbits == 64 else 0.5
     pairs = DIGIT_PAIRS if kbits == 64 else 36
     spdz = mode == "spdz2k"
@@ -111,7 +123,23 @@ def stage_work(stage: str, specs, mode: str, f: int = 0, kbits: int = 64, compre
         elem = 64 * n + 16                  # 4 n share arrays read, one opened value written
         nops = (2 * n + 1) if spdz else (n + 1)  # packed operands per side
         fused = n == 2 and wide and not conv     # U opened and right operands packed in one pass
-        if stage == "open_u":
+        opened = rns and fused and (spdz or not along_m(s, compress))  # E and U opened with their planes
+        outs = (2 * n if spdz else n) * mn
+        if rns and stage in ("open_pack", "pack"):
+            pass
+        elif stage == "rns_open":
+            tot += (elem + 36 * nops) * kn + (80 + 36 * nops + (32 if spdz else 0)) * mk if opened else 0
+        elif stage == "rns_pack":
+            tot += nops * (52 * mk + 16 * nr + 36 * kn) if wide and not opened else 0
+        elif stage == "rns_gemm":
+            tot += 2 * 36 * (4 if spdz else 2) * n * M * K * N if wide else 0
+        elif stage == "rns_fold":
+            tot += 68 * outs if wide else 0
+        elif opened and stage == "row_pass":
+            tot += 80 * mk
+        elif rns and fused and not opened and stage == "open_u":
+            tot += elem * nr
+        elif stage == "open_u":
             tot += 0 if fused else elem * nr
         elif stage == "open_pack":
             tot += (elem + 48) * kn if fused else 0
@@ -132,15 +160,17 @@ def stage_work(stage: str, specs, mode: str, f: int = 0, kbits: int = 64, compre
             tot += (16 * n + 16) * kn if not spdz and along_m(s, compress) else 0
         else:
             return None
-    if stage == "ring_gemm":
+    if stage in ("ring_gemm", "rns_gemm"):
         return ("mfma", tot)
     return ("hbm", int(tot * scale))
 
 
+RNS_STAGES = ("rns_open", "rns_pack", "rns_gemm", "rns_fold")
+
 # Sources that determine what the device kernels do; the hardware counters in
 # profiles/traffic.json are valid only for the digest they were taken on.
 KERNEL_SOURCES = ("ct_device.h", "ct_internal.h", "ct_sweep.h", "ct_passes.h", "ct_kernels.hip", "ct_gemm.hip",
-                  "ct_parties.hip")
+                  "ct_parties.hip", "ct_rns.h", "ct_rns.hip")
 
 
 def strip_comments(src: str) -> str:
@@ -509,9 +539,15 @@ def main():
 
     # per-stage figures and the dominant kernel's roofline
     stage_rows = {}
+    rns = "rns_gemm" in stages
     for name, (tot_ms, n) in stages.items():
+        if name in RNS_STAGES:
+            n = args.steps  # the launches of a step's groups taken together
         avg = tot_ms / max(n, 1)
-        w = stage_work(name, specs, args.mode, args.f, args.kbits, args.compress, implicit, args.parties)
+        w = stage_work(name, specs, args.mode, args.f, args.kbits, args.compress, implicit, args.parties, rns)
+        # a batch on both product paths: which layers are on which is not known here
+        if rns and "ring_gemm" in stages and name in ("open_u", "open_pack", "pack", "row_pass", "ring_gemm") + RNS_STAGES:
+            w = None
         row = {"ms_per_launch": round(avg, 5), "launches": n, "share_of_step": round(tot_ms / args.steps / ms, 4)}
         if w is not None and w[1] > 0:
             bound, units = w

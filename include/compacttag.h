@@ -183,7 +183,9 @@ typedef struct {
  * [Delta]_p = draw(key_seed, stream (0xFFFF << 16) | (0x40 + p), 0) (F_MAC
  * Initialize, Appendix A) and keeps them resident, and allocates the
  * context's own fixed-size device scratch (descriptor tables, check
- * accumulators).  *out receives the context; free it with ct_destroy. */
+ * accumulators and, with k = s = 64, just under 2 GiB for the residues of
+ * large products; a context that cannot have these forms every product by
+ * digits).  *out receives the context; free it with ct_destroy. */
 ct_status ct_create(ct_ctx **out, const ct_params *params);
 
 /* Releases the context and its scratch after synchronizing its stream. */
@@ -237,7 +239,9 @@ ct_status ct_mac_check_device(ct_ctx *ctx, ct_mode mode, const ct_layer_desc *L,
  * layers with N <= CT_SKINNY_N runs the former on a second stream of the
  * context, forked from the context stream after its earlier work and joined
  * back before its later work, so the two groups overlap; every check record
- * still lands at its layer's position in out_dev.  With per-kernel timing
+ * still lands at its layer's position in out_dev.  The same stream also takes
+ * the residue products of a batch that forms them in several groups, beside
+ * the openings of the next group (ct_tag_linear too).  With per-kernel timing
  * enabled (ct_set_timing) the whole batch runs on the context stream. */
 ct_status ct_tag_linear_check(ct_ctx *ctx, ct_mode mode, const ct_layer_desc *L, const ct_layer_bufs *B, int n,
                               ct_check_result *out_dev);
@@ -277,8 +281,9 @@ ct_status ct_mac_check(ct_ctx *ctx, ct_mode mode, const ct_layer_desc *L, const 
 ct_status ct_set_timing(ct_ctx *ctx, int enable);
 
 /* Whether ct_tag_linear_check and plans created afterwards run the two
- * layer groups of a mixed batch on two streams (enable != 0, the default) or
- * the whole batch on the context stream (0: every kernel then runs alone,
+ * layer groups of a mixed batch, and the residue products of one group of
+ * layers and the openings of the next, on two streams (enable != 0, the
+ * default; ct_tag_linear the latter only) or the whole batch on the context stream (0: every kernel then runs alone,
  * as a per-kernel profile needs).  Results are the same either way. */
 ct_status ct_set_overlap(ct_ctx *ctx, int enable);
 
@@ -326,7 +331,11 @@ typedef struct {
  * *count receives the number of stages), then resets the totals. */
 ct_status ct_stage_times(ct_ctx *ctx, ct_stage_time *out, int max, int *count);
 
-/* Product kernel and workgroup tile shape (ct_tuning.tile).  Both kernels
+/* Product kernel and workgroup tile shape (ct_tuning.tile) of products formed
+ * by digits.  With k = s = 64, CT_TILE_AUTO set by ct_set_tuning (the default)
+ * and staged launches, the products of layers where it is faster go through
+ * residues instead (36 int8 products per multiplication, not 136), whatever
+ * ct_autotune chose; the request server's batches never do.  All kernels
  * compute the same exact products (identical results); a workgroup of four
  * wavefronts owns 64 x 64 outputs, or 128 x 64 with two 32 x 32 tiles per
  * wavefront, which only the k = s = 32 set has registers for (with
@@ -395,8 +404,9 @@ ct_status ct_set_tuning(ct_ctx *ctx, const ct_tuning *t);
  * for the batch at creation time) are bound at creation; every launch
  * recomputes all outputs from the current contents of the input buffers.
  * A mixed batch is captured as two branches of the graph, as
- * ct_tag_linear_check runs it on two streams.  Creating a plan allocates;
- * launching one does not. */
+ * ct_tag_linear_check runs it on two streams.  Creating a plan allocates
+ * (its tables and what its products by residues need, below 2 GiB); launching
+ * one does not. */
 typedef struct ct_plan ct_plan;
 
 /* Validates as ct_tag_linear_check does (out_dev may be NULL: no

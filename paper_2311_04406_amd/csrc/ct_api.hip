@@ -25,12 +25,14 @@ using namespace ct;
 static const char *kStageNames[ST_COUNT] = {
     "deal_lift", "fill_zero", "deal_auth", "deal_skinny", "zero_acc", "open_u", "row_pass", "pack",
     "copy_base", "ring_gemm", "post", "compact_final", "check_batch", "check_compact", "finalize", "col_tag",
-    "conv_compress", "np_open", "np_skinny", "np_compress", "np_gemv", "open_pack", "persistent"};
+    "conv_compress", "np_open", "np_skinny", "np_compress", "np_gemv", "open_pack", "persistent",
+    "rns_open", "rns_pack", "rns_gemm", "rns_fold"};
 constexpr int EV_POOL = 2048;
 
 struct ct_plan {
     ct_ctx *ctx = nullptr;
     Lane lane, side;  // side: the matrix-core layers of a mixed batch (forked in the graph)
+    RnsMemory rns;  // of both lanes
     hipEvent_t fork = nullptr, join = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -303,7 +305,18 @@ ct_status stage_layers(ct_ctx *c, Lane &ln, const ct_layer_desc *L, const ct_lay
     return CT_OK;
 }
 
-ct_status upload(ct_ctx *c, Lane &ln, int n, int nprobs, int njobs = 0, int nskinny = 0) {
+ct_status upload(ct_ctx *c, Lane &ln, int n, int nprobs, int njobs = 0, int nskinny = 0,
+                 const RnsPlan &rns = RnsPlan()) {
+    if (rns.nprobs > 0) {
+        HIPCHK(c, hipMemcpyAsync(ln.rns_probs_dev, ln.rns_probs_host, sizeof(RnsProb) * rns.nprobs,
+                                 hipMemcpyHostToDevice, ln.stream));
+        if (rns.njobs > 0)
+            HIPCHK(c, hipMemcpyAsync(ln.rns_jobs_dev, ln.rns_jobs_host, sizeof(RnsJob) * rns.njobs,
+                                     hipMemcpyHostToDevice, ln.stream));
+        if (rns.nopen > 0)
+            HIPCHK(c, hipMemcpyAsync(ln.rns_open_dev, ln.rns_open_host, sizeof(RnsOpen) * rns.nopen,
+                                     hipMemcpyHostToDevice, ln.stream));
+    }
     HIPCHK(c, hipMemcpyAsync(ln.layers_dev, ln.layers_host, sizeof(LayerDev) * n, hipMemcpyHostToDevice, ln.stream));
     if (nprobs > 0)
         HIPCHK(c, hipMemcpyAsync(ln.gemm_dev, ln.gemm_host, sizeof(GemmProb) * nprobs, hipMemcpyHostToDevice,
@@ -371,6 +384,63 @@ PackJob make_job(const u128 *src, u128 *dst, int64_t rows, int64_t cols, int sid
     j.kt = (int32_t)((K + 31) / 32);
     j.tiles = j.majt * j.kt;
     return j;
+}
+
+// ---- products through residues (ct_rns.h) ----
+
+// The residue path serves Z_{2^128}; a product kernel named by ct_set_tuning
+// and the persistent launch, which walks the digit path's stages, keep every
+// product on the digit path.
+bool rns_allowed(const ct_ctx *c) {
+    return c->eb == 16 && c->fallback.tile == CT_TILE_AUTO && c->launch_mode == CT_LAUNCH_STAGED;
+}
+// The products of the online phase of a layer with n parties: E [B]_p +
+// ([A]_p or A_0 + E) U, in SPDZ2k also E [tB]_p + ([tA]_p + [Delta]_p E) U.
+RnsShape rns_online_shape(const ct_layer_desc &d, int np, bool compact) {
+    RnsShape s;
+    s.M = d.M; s.K = d.K; s.N = d.N;
+    s.nl = s.nr = compact ? np + 1 : 2 * np + 1;
+    s.outs = compact ? np : 2 * np;
+    if (np == 2 && compact) {
+        const bool cm = CT_COMPRESS_ALONG_M(d.M, d.N, d.compress);
+        // the one pass that opens, compresses and converts; convolutions are converted from memory on both paths
+        s.rate = d.conv_c != 0 ? 1.0e5 : cm ? s.rate : 1.38e5;
+        // only layers compressed along M open U apart from its conversion here and together with it there
+        if (d.conv_c == 0 && cm) s.refetch = 48.0 * d.K * d.N;
+    }
+    return s;
+}
+
+// Scratch of m.bytes; without it (m.bytes = 0) every product runs by digits.
+bool rns_alloc(RnsMemory &m) {
+    if (hipMalloc(&m.scratch, m.bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    m.scratch = nullptr;
+    m.bytes = 0;
+    return false;
+}
+
+// take[l]: layer l's online products go through residues.
+std::vector<char> rns_layers(const ct_ctx *c, const Lane &ln, ct_mode mode, const ct_layer_desc *L, int n) {
+    std::vector<char> take(n, 0);
+    if (!rns_allowed(c) || !ln.rns || ln.rns->bytes <= 0) return take;
+    std::vector<RnsShape> s;
+    std::vector<int> at;
+    for (int l = 0; l < n; l++)
+        if (L[l].N > SKINNY_MAX_N) {
+            s.push_back(rns_online_shape(L[l], c->np, mode == CT_MODE_COMPACT));
+            at.push_back(l);
+        }
+    const std::vector<char> t = rns_choose(s, ln.rns->bytes);
+    int64_t need = 0;
+    for (size_t i = 0; i < at.size(); i++)
+        if (t[i]) need += rns_align(s[i].bytes(s[i].chunk_len(1)));
+    if (need > 0 && !ln.rns->scratch) {
+        ln.rns->bytes = std::min(ln.rns->bytes, need);
+        if (!rns_alloc(*ln.rns)) return take;
+    }
+    for (size_t i = 0; i < at.size(); i++) take[at[i]] = t[i];
+    return take;
 }
 
 // Assigns tile ranges to packing jobs; returns the total tile count.
@@ -484,10 +554,71 @@ int plan_gemms(std::vector<GemmProb> &probs, int num_cus, const GemmTuning &tu, 
     return (int)probs.size();
 }
 
-ct_status run_gemms(ct_ctx *c, Lane &ln, int nprobs, int total_tiles, const GemmTuning &tu) {
+ct_status run_gemms(ct_ctx *c, Lane &ln, int nprobs, int total_tiles, const GemmTuning &tu, hipStream_t st) {
     if (nprobs > 0)
         LAUNCH(c, ln, ST_RING_GEMM, launch_gemm(c->eb, ln.gemm_dev, nprobs, total_tiles, tu.xcd_remap,
-                                                ln.gemm_host[0].mt, gemm_kernel(tu), ln.stream));
+                                                ln.gemm_host[0].mt, gemm_kernel(tu), st));
+    return CT_OK;
+}
+
+// The products of a call whose other passes before them are enqueued: the
+// digit products, then the openings, conversions and products through
+// residues, group by group.  With several groups (and overlap on) the products
+// run on the lane's aux stream, beside the openings of the next group:
+// those are bound by HBM, the products mostly by the matrix cores.
+// join_products must follow on the lane's stream.
+bool overlap_products(const ct_ctx *c, const Lane &ln, const OnlineLaunch &P) {
+    return c->overlap && ln.aux && !(c->timing && ln.timed) && P.rns.groups.size() > 1;
+}
+
+ct_status run_products(ct_ctx *c, Lane &ln, const OnlineLaunch &P, bool over) {
+    const hipStream_t main = ln.stream, prod = over ? ln.aux : main;
+    // what the lane's stream holds so far comes before the products enqueued next
+    auto ready = [&]() -> hipError_t {
+        if (!over) return hipSuccess;
+        const hipError_t e = hipEventRecord(ln.ev_ready, main);
+        return e != hipSuccess ? e : hipStreamWaitEvent(prod, ln.ev_ready, 0);
+    };
+    bool used[2] = {false, false};  // halves of the scratch that products still read
+    auto wait_free = [&](int half) -> hipError_t {
+        if (!used[half]) return hipSuccess;
+        used[half] = false;
+        return hipStreamWaitEvent(main, ln.ev_free[half], 0);
+    };
+    auto leave = [&](int half) -> hipError_t {
+        used[half] = over;
+        return over ? hipEventRecord(ln.ev_free[half], prod) : hipSuccess;
+    };
+    HIPCHK(c, ready());
+    ct_status s = run_gemms(c, ln, P.nm, P.total_tiles, P.tu, prod);
+    if (s != CT_OK) return s;
+    for (const RnsGroup &G : P.rns.groups) {
+        const RnsProb *probs = ln.rns_probs_dev + G.prob0;
+        HIPCHK(c, wait_free(G.half));
+        if (G.whole) HIPCHK(c, wait_free(1));
+        for (int k = 0; k < G.chunks; k++) {
+            if (k > 0) HIPCHK(c, wait_free(0));  // the planes of the chunk before
+            if (G.nopen > 0)
+                LAUNCH(c, ln, ST_RNS_OPEN, launch_rns_open(ln.layers_dev, ln.rns_open_dev + G.open0, G.nopen, G.left, G.right,
+                                                           P.flags, k, main));
+            if (G.njobs > 0) LAUNCH(c, ln, ST_RNS_PACK, launch_rns_pack(ln.rns_jobs_dev + G.job0, G.njobs, G.wgs, k, main));
+            HIPCHK(c, ready());
+            if (G.n2 > 0) LAUNCH(c, ln, ST_RNS_GEMM, launch_rns_gemm(2, probs, G.n2, G.blocks2, k, prod));
+            if (G.n1 > 0) LAUNCH(c, ln, ST_RNS_GEMM, launch_rns_gemm(1, probs + G.n2, G.n1, G.blocks1, k, prod));
+            if (k + 1 < G.chunks) HIPCHK(c, leave(0));
+        }
+        LAUNCH(c, ln, ST_RNS_FOLD, launch_rns_fold(probs, G.n2 + G.n1, G.fold_items, prod));
+        HIPCHK(c, leave(G.half));
+        if (G.whole) HIPCHK(c, leave(1));
+    }
+    return CT_OK;
+}
+
+// The lane's stream after the products.
+ct_status join_products(ct_ctx *c, Lane &ln, bool over) {
+    if (!over) return CT_OK;
+    HIPCHK(c, hipEventRecord(ln.ev_join, ln.aux));
+    HIPCHK(c, hipStreamWaitEvent(ln.stream, ln.ev_join, 0));
     return CT_OK;
 }
 
@@ -506,9 +637,9 @@ hipError_t lane_init(Lane &ln, hipStream_t stream, int max_layers) {
     // up to two products per party and 4 n + 2 packed operands per layer
     ln.max_probs = 2 * CT_MAX_PARTIES * max_layers;
     ln.max_jobs = (4 * CT_MAX_PARTIES + 2) * max_layers;
-    hipError_t e;
+    hipError_t err;
 #define LANE_TRY(expr) \
-    if ((e = (expr)) != hipSuccess) return e
+    if ((err = (expr)) != hipSuccess) return err
     LANE_TRY(hipMalloc(&ln.layers_dev, sizeof(LayerDev) * ln.max_layers));
     LANE_TRY(hipMalloc(&ln.gemm_dev, sizeof(GemmProb) * ln.max_probs));
     LANE_TRY(hipMalloc(&ln.pack_dev, sizeof(PackJob) * ln.max_jobs));
@@ -521,14 +652,32 @@ hipError_t lane_init(Lane &ln, hipStream_t stream, int max_layers) {
     LANE_TRY(hipHostMalloc(&ln.pack_host, sizeof(PackJob) * ln.max_jobs, hipHostMallocDefault));
     LANE_TRY(hipHostMalloc(&ln.skinny_host, sizeof(SkinnyProb) * ln.max_layers, hipHostMallocDefault));
     LANE_TRY(hipHostMalloc(&ln.res_host, sizeof(ct_check_result) * ln.max_layers, hipHostMallocDefault));
+    if (ln.rns) {
+        const int64_t open = rns_align(sizeof(RnsOpen) * ln.max_layers), jobs = rns_align(sizeof(RnsJob) * ln.max_jobs),
+                      probs = rns_align(sizeof(RnsProb) * ln.max_probs);
+        LANE_TRY(hipMalloc(&ln.rns_tables, open + jobs + probs));
+        LANE_TRY(hipHostMalloc(&ln.rns_staging, open + jobs + probs, hipHostMallocDefault));
+        ln.rns_open_dev = reinterpret_cast<RnsOpen *>(ln.rns_tables);
+        ln.rns_jobs_dev = reinterpret_cast<RnsJob *>(ln.rns_tables + open);
+        ln.rns_probs_dev = reinterpret_cast<RnsProb *>(ln.rns_tables + open + jobs);
+        ln.rns_open_host = reinterpret_cast<RnsOpen *>(ln.rns_staging);
+        ln.rns_jobs_host = reinterpret_cast<RnsJob *>(ln.rns_staging + open);
+        ln.rns_probs_host = reinterpret_cast<RnsProb *>(ln.rns_staging + open + jobs);
+    }
     LANE_TRY(hipEventCreateWithFlags(&ln.upload_done, hipEventDisableTiming));
     LANE_TRY(hipEventRecord(ln.upload_done, ln.stream));
+    for (hipEvent_t *e : {&ln.ev_ready, &ln.ev_free[0], &ln.ev_free[1], &ln.ev_join})
+        LANE_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
 #undef LANE_TRY
     return hipSuccess;
 }
 
 void lane_free(Lane &ln) {
     if (ln.upload_done) (void)hipEventDestroy(ln.upload_done);
+    for (hipEvent_t e : {ln.ev_ready, ln.ev_free[0], ln.ev_free[1], ln.ev_join})
+        if (e) (void)hipEventDestroy(e);
+    if (ln.rns_tables) (void)hipFree(ln.rns_tables);
+    if (ln.rns_staging) (void)hipHostFree(ln.rns_staging);
     if (ln.sync_dev) (void)hipFree(ln.sync_dev);
     if (ln.layers_dev) (void)hipFree(ln.layers_dev);
     if (ln.gemm_dev) (void)hipFree(ln.gemm_dev);
@@ -571,6 +720,7 @@ ct_status ct_create(ct_ctx **out, const ct_params *p) {
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) == hipSuccess && cus > 0)
             c->num_cus = cus;
         const int ml = p->max_layers > 0 ? p->max_layers : 256;
+        if (c->eb == 16 && rns_alloc(c->rns)) c->main.rns = c->side.rns = &c->rns;
         e = lane_init(c->main, reinterpret_cast<hipStream_t>(p->hip_stream), ml);
         hipStream_t side = nullptr;
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
@@ -580,6 +730,7 @@ ct_status ct_create(ct_ctx **out, const ct_params *p) {
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->join, hipEventDisableTiming);
         if (e == hipSuccess) e = scratch_address(c->device, &c->static_work);
         if (e == hipSuccess) c->static_bufs.resize(ml);
+        c->main.aux = side;
     }
     if (e != hipSuccess) {
         std::fprintf(stderr, "ct_create: %s\n", hipGetErrorString(e));
@@ -599,6 +750,7 @@ ct_status ct_destroy(ct_ctx *c) {
     for (auto e : c->ev_end) (void)hipEventDestroy(e);
     if (c->fork) (void)hipEventDestroy(c->fork);
     if (c->join) (void)hipEventDestroy(c->join);
+    if (c->rns.scratch) (void)hipFree(c->rns.scratch);
     lane_free(c->main);
     hipStream_t side = c->side.stream;
     lane_free(c->side);
@@ -662,7 +814,7 @@ ct_status ct::run_deal(ct_ctx *c, Lane &ln, const ct_layer_desc *L, const ct_lay
     for (int i = 0; i < nm; i++)
         if (probs[i].accumulate)
             LAUNCH(c, ln, ST_FILL_ZERO, launch_fill_zero(c->eb, probs[i].out, (int64_t)probs[i].M * probs[i].N, ln.stream));
-    if ((s = run_gemms(c, ln, nm, total_tiles, tu)) != CT_OK) return s;
+    if ((s = run_gemms(c, ln, nm, total_tiles, tu, ln.stream)) != CT_OK) return s;
     if (nskinny > 0) {
         int max_rows = 0;
         for (int i = 0; i < nskinny; i++) max_rows = std::max(max_rows, ln.skinny_host[i].M);
@@ -698,6 +850,8 @@ ct_status prepare_online_np(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_de
     const bool compact = mode == CT_MODE_COMPACT, check = out_dev != nullptr;
     const int np = c->np;
     std::vector<GemmProb> probs;
+    std::vector<RnsLayer> rns;
+    const std::vector<char> take = rns_layers(c, ln, mode, L, n);
     int njobs = 0;
     PackJob *J = ln.pack_host;
     for (int l = 0; l < n; l++) {
@@ -708,6 +862,34 @@ ct_status prepare_online_np(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_de
         if (njobs + 4 * np + 2 > ln.max_jobs || (int)probs.size() + 2 * np > ln.max_probs)
             return fail(c, CT_EINVAL, "internal error: layer tables too small");
         auto wp = [&](int64_t e) { return elem_at(o.work, e, c->eb); };
+        if (take[l]) {
+            // operands: E, A_0 + E, [A]_1 .. (0 .. np), [B]_p, U (np + 1 .. 2 np + 1); SPDZ2k then the
+            // folded tag operands and [tB]_p; products of two parties share E and U
+            RnsLayer r;
+            r.shape = rns_online_shape(d, np, compact);
+            r.ops.push_back({o.E, 0});
+            r.ops.push_back({wp(0), 0});
+            for (int p = 1; p < np; p++) r.ops.push_back({o.A[p], 0});
+            for (int p = 0; p < np; p++) r.ops.push_back({o.B[p], 1});
+            r.ops.push_back({o.U, 1});
+            const int ou = 2 * np + 1;
+            auto pairs = [&](int left, int right, u128 *const *base, u128 *const *out) {
+                for (int p = 0; p < np; p += 2) {
+                    const bool two = p + 1 < np;
+                    r.prods.push_back({two ? 2 : 1, 0, left + p, two ? left + p + 1 : -1, right + p,
+                                       two ? right + p + 1 : -1, ou, {base[p], two ? base[p + 1] : nullptr},
+                                       {out[p], two ? out[p + 1] : nullptr}});
+                }
+            };
+            pairs(1, np + 1, o.C, o.Z);
+            if (!compact) {
+                for (int p = 0; p < np; p++) r.ops.push_back({wp(w.fold_tA(p)), 0});
+                for (int p = 0; p < np; p++) r.ops.push_back({o.tB[p], 1});
+                pairs(ou + 1, ou + 1 + np, o.tC, o.tZ);
+            }
+            rns.push_back(std::move(r));
+            continue;
+        }
         const int first_job = njobs;
         J[njobs++] = make_job(o.E, wp(w.left(0)), d.M, d.K, 0);
         J[njobs++] = make_job(wp(0), wp(w.left(1)), d.M, d.K, 0);  // A_0 + E
@@ -741,7 +923,9 @@ ct_status prepare_online_np(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_de
     P.tu = tuning_for(c, shape_class(mode, L, n));
     P.nm = plan_gemms(probs, c->num_cus, P.tu, &P.total_tiles, &P.any_accum, c->eb);
     std::copy(probs.begin(), probs.end(), ln.gemm_host);
-    ct_status s = upload(c, ln, n, P.nm, njobs);
+    if (!rns.empty())
+        rns_plan(rns, ln.rns->scratch, ln.rns->bytes, ln.rns_jobs_host, ln.rns_probs_host, ln.rns_open_host, P.rns);
+    ct_status s = upload(c, ln, n, P.nm, njobs, 0, P.rns);
     if (s != CT_OK) return s;
     P.flags = (check ? F_CHECK : 0) | (compact ? F_COMPACT : F_SPDZ);
     bool fused_skinny = false;
@@ -783,8 +967,10 @@ ct_status enqueue_online_np(ct_ctx *c, Lane &ln, const OnlineLaunch &P) {
     if (P.any_unfused) LAUNCH(c, ln, ST_NP_OPEN, launch_np_open(c->eb, ln.layers_dev, n, 1, P.flags, P.max_open, ln.stream));
     if (P.njobs > 0) LAUNCH(c, ln, ST_PACK, launch_pack(c->eb, ln.pack_dev, P.njobs, P.pack_tiles, ln.stream));
     if (P.any_accum) LAUNCH(c, ln, ST_COPY_BASE, launch_prob_base(c->eb, ln.gemm_dev, P.nm, P.max_mn, ln.stream));
-    ct_status s = run_gemms(c, ln, P.nm, P.total_tiles, P.tu);
-    if (s != CT_OK) return s;
+    const bool over = overlap_products(c, ln, P);
+    ct_status s = run_products(c, ln, P, over);
+    const ct_status j = join_products(c, ln, over);  // also on failure, so that the streams stay joined
+    if (s != CT_OK || (s = j) != CT_OK) return s;
     if (P.any_unfused)
         LAUNCH(c, ln, ST_NP_SKINNY, launch_np_skinny(c->eb, ln.layers_dev, n, P.flags, P.max_skinny_items, ln.stream));
     LAUNCH(c, ln, ST_POST, launch_np_post(c->eb, ln.layers_dev, n, P.flags, P.max_mn, ln.stream));
@@ -820,6 +1006,8 @@ ct_status prepare_online(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_desc 
     // SPDZ2k tags of Eq. (3):  [tZ]_p = [tC]_p + E [tB]_p + ([tA]_p + [Delta]_p E) U.
     // Every operand is converted once into digit tiles in the workspace.
     std::vector<GemmProb> probs;
+    std::vector<RnsLayer> rns;
+    const std::vector<char> take = rns_layers(c, ln, mode, L, n);
     probs.reserve(4 * n);
     int njobs = 0;
     int64_t open_tiles = 0;
@@ -830,6 +1018,25 @@ ct_status prepare_online(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_desc 
         const WorkOff w = work_off(d.M, d.K, d.N);
         u128 *W = o.work;
         auto wp = [&](int64_t e) { return elem_at(W, e, c->eb); };
+        if (take[l]) {
+            // layers that are neither convolutions nor compressed along M open E and U with their planes; the
+            // others' E, A_0 + E (and the folded tag operands) come from the pass over M x K
+            const bool open = !(compact && o.cm) && !o.cv.on;
+            RnsLayer r;
+            r.shape = rns_online_shape(d, c->np, compact);
+            r.cv = o.cv.on ? &o.cv : nullptr;
+            r.open = open ? l : -1;
+            r.ops = {{o.E, 0}, {wp(w.AE0), 0}, {o.A[1], 0}, {o.B[0], 1}, {o.B[1], 1}, {o.U, 1}};
+            r.prods = {{2, 0, 1, 2, 3, 4, 5, {o.C[0], o.C[1]}, {o.Z[0], o.Z[1]}}};
+            if (!compact) {
+                const RnsOperand tag[4] = {{wp(w.tAE0), 0}, {wp(w.tAE1), 0}, {o.tB[0], 1}, {o.tB[1], 1}};
+                r.ops.insert(r.ops.end(), tag, tag + 4);
+                r.prods.push_back({2, 0, 6, 7, 8, 9, 5, {o.tC[0], o.tC[1]}, {o.tZ[0], o.tZ[1]}});
+            }
+            if (open) ln.layers_host[l].fo = FO_RNS;
+            rns.push_back(std::move(r));
+            continue;
+        }
         const int first_job = njobs;
         PackJob *J = ln.pack_host;
         J[njobs++] = make_job(o.E, wp(w.Ep), d.M, d.K, 0);
@@ -843,7 +1050,7 @@ ct_status prepare_online(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_desc 
                 if (!job_in_work(j, W, d, c->eb))
                     return fail(c, CT_EINVAL, "internal error: workspace layout exceeds CT_WORK_LEN");
             LayerDev &lh = ln.layers_host[l];
-            lh.fo = 1;
+            lh.fo = FO_DIGITS;
             lh.rp[0] = wp(w.B0p);
             lh.rp[1] = wp(w.B1p);
             lh.rp[2] = wp(w.Up);
@@ -877,12 +1084,14 @@ ct_status prepare_online(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_desc 
     P.out_dev = out_dev;
     P.njobs = njobs;
     P.open_tiles = (int)open_tiles;
-    for (int l = 0; l < n; l++) P.any_open_u |= !ln.layers_host[l].fo;
+    for (int l = 0; l < n; l++) P.any_open_u |= ln.layers_host[l].fo == FO_NONE;
     P.pack_tiles = plan_jobs(ln.pack_host, njobs);
     P.tu = tuning_for(c, shape_class(mode, L, n));
     P.nm = plan_gemms(probs, c->num_cus, P.tu, &P.total_tiles, &P.any_accum, c->eb);
     std::copy(probs.begin(), probs.end(), ln.gemm_host);
-    if ((s = upload(c, ln, n, P.nm, njobs)) != CT_OK) return s;
+    if (!rns.empty())
+        rns_plan(rns, ln.rns->scratch, ln.rns->bytes, ln.rns_jobs_host, ln.rns_probs_host, ln.rns_open_host, P.rns);
+    if ((s = upload(c, ln, n, P.nm, njobs, 0, P.rns)) != CT_OK) return s;
 
     const Sizes sz = max_sizes(L, n);
     P.max_zero = std::max(compact ? sz.cvec : 0, sz.skinny_mn);
@@ -901,7 +1110,8 @@ ct_status prepare_online(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_desc 
     for (int l = 0; l < n; l++) {
         const int64_t N = L[l].N;
         const int v = N > SKINNY_MAX_N ? 0 : (N <= 1 ? 1 : (N <= 2 ? 2 : (N <= 4 ? 4 : SKINNY_MAX_N)));
-        P.variants |= 1 << (compact && CT_COMPRESS_ALONG_M(L[l].M, N, L[l].compress) ? VARIANT_CM + v : v);
+        if (ln.layers_host[l].fo == FO_RNS) P.variants |= 1 << VARIANT_E;
+        else P.variants |= 1 << (compact && CT_COMPRESS_ALONG_M(L[l].M, N, L[l].compress) ? VARIANT_CM + v : v);
     }
     return CT_OK;
 }
@@ -951,13 +1161,24 @@ ct_status enqueue_online(ct_ctx *c, Lane &ln, const OnlineLaunch &P) {
         LAUNCH(c, ln, ST_OPEN_PACK, launch_open_pack(c->eb, ln.layers_dev, n, P.flags, P.open_tiles, ln.stream));
     if (P.any_conv_n)
         LAUNCH(c, ln, ST_CONV_COMPRESS, launch_conv_compress(c->eb, ln.layers_dev, n, P.max_conv_items, ln.stream));
-    LAUNCH(c, ln, ST_ROW_PASS, launch_row_pass(c->eb, ln.layers_dev, n, P.flags, P.max_row_items, P.variants, ln.stream));
+    // the pass of the layers whose E the conversion opens comes after it
+    const int late = P.variants & (1 << VARIANT_E), early = P.variants & ~late;
+    if (early)
+        LAUNCH(c, ln, ST_ROW_PASS, launch_row_pass(c->eb, ln.layers_dev, n, P.flags, P.max_row_items, early, ln.stream));
     if (P.any_cm) LAUNCH(c, ln, ST_COL_TAG, launch_col_tag(c->eb, ln.layers_dev, n, P.max_col_tag, ln.stream));
     if (P.njobs > 0) LAUNCH(c, ln, ST_PACK, launch_pack(c->eb, ln.pack_dev, P.njobs, P.pack_tiles, ln.stream));
     if (P.any_accum)
         LAUNCH(c, ln, ST_COPY_BASE, launch_prob_base(c->eb, ln.gemm_dev, P.nm, P.max_mn, ln.stream));
-    ct_status s = run_gemms(c, ln, P.nm, P.total_tiles, P.tu);
-    if (s != CT_OK) return s;
+    const bool over = overlap_products(c, ln, P);
+    auto products = [&]() -> ct_status {
+        const ct_status s = run_products(c, ln, P, over);
+        if (s == CT_OK && late)
+            LAUNCH(c, ln, ST_ROW_PASS, launch_row_pass(c->eb, ln.layers_dev, n, P.flags, P.max_row_items, late, ln.stream));
+        return s;
+    };
+    ct_status s = products();
+    const ct_status j = join_products(c, ln, over);  // also on failure, so that the streams stay joined
+    if (s != CT_OK || (s = j) != CT_OK) return s;
     LAUNCH(c, ln, ST_POST, launch_post(c->eb, ln.layers_dev, n, P.flags, P.max_mn_items, ln.stream));
     if (P.compact) LAUNCH(c, ln, ST_COMPACT_FINAL, launch_compact_final(c->eb, ln.layers_dev, n, P.flags, ln.stream));
     if (P.check) LAUNCH(c, ln, ST_FINALIZE, launch_finalize(c->eb, ln.layers_dev, n, P.out_dev, ln.stream));
@@ -1124,6 +1345,7 @@ ct_status ct_plan_create(ct_ctx *c, ct_mode mode, const ct_layer_desc *L, const 
     ct_plan *pl = new ct_plan();
     pl->ctx = c;
     hipStream_t st = nullptr, side = nullptr;
+    if (c->rns.scratch) pl->lane.rns = pl->side.rns = &pl->rns;
     hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
     if (e == hipSuccess) e = lane_init(pl->lane, st, std::max(n, 1));
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
@@ -1135,6 +1357,7 @@ ct_status ct_plan_create(ct_ctx *c, ct_mode mode, const ct_layer_desc *L, const 
         ct_plan_destroy(pl);
         return hip_fail(c, e, "ct_plan_create");
     }
+    pl->lane.aux = side;
     OnlineLaunch Pa, Pb;
     bool split = false;
     ct_status s = prepare_online_split(c, pl->lane, pl->side, mode, L, B, n, out_dev, Pa, Pb, split);
@@ -1180,6 +1403,7 @@ ct_status ct_plan_destroy(ct_plan *pl) {
     if (pl->graph) (void)hipGraphDestroy(pl->graph);
     if (pl->fork) (void)hipEventDestroy(pl->fork);
     if (pl->join) (void)hipEventDestroy(pl->join);
+    if (pl->rns.scratch) (void)hipFree(pl->rns.scratch);
     hipStream_t st = pl->lane.stream, side = pl->side.stream;
     lane_free(pl->lane);
     lane_free(pl->side);
@@ -1276,13 +1500,14 @@ ct_status ct_autotune(ct_ctx *c, ct_mode mode, const ct_layer_desc *L, const ct_
         ct_status st = run_online(c, c->main, mode, L, B, n, nullptr);  // warm-up
         if (st == CT_OK) {
             HIPCHK(c, fold_timing(c));
-            for (int k : {ST_RING_GEMM, ST_COPY_BASE}) c->stage_ms[k] = 0, c->stage_n[k] = 0;
+            for (int k : {ST_RING_GEMM, ST_COPY_BASE, ST_RNS_GEMM, ST_RNS_FOLD}) c->stage_ms[k] = 0, c->stage_n[k] = 0;
             for (int r = 0; r < reps && st == CT_OK; r++) st = run_online(c, c->main, mode, L, B, n, nullptr);
         }
         if (st == CT_OK) {
             HIPCHK(c, fold_timing(c));
-            const double ms = (c->stage_ms[ST_RING_GEMM] + c->stage_ms[ST_COPY_BASE]) / reps;
-            if (c->stage_n[ST_RING_GEMM] > 0 && ms < best_ms) {
+            const double ms = (c->stage_ms[ST_RING_GEMM] + c->stage_ms[ST_COPY_BASE] + c->stage_ms[ST_RNS_GEMM] +
+                               c->stage_ms[ST_RNS_FOLD]) / reps;
+            if (c->stage_n[ST_RING_GEMM] + c->stage_n[ST_RNS_GEMM] > 0 && ms < best_ms) {
                 best_ms = ms;
                 best = cand;
             }

@@ -231,7 +231,7 @@ __device__ __forceinline__ void open_pack_body(const LayerDev *__restrict__ Ls, 
     __shared__ __attribute__((aligned(16))) uint8_t tile[Tile<R>::OPB];
     __shared__ R sh[3 * WAVES];
     const LayerDev &L = Ls[g.y];
-    if (!L.fo) return;
+    if (L.fo != FO_DIGITS) return;
     const int64_t K = L.K, N = L.N;
     const int kt = (int)((K + 31) / 32), tiles = (int)((N + 63) / 64) * kt;
     if ((int)g.x >= tiles) return;
@@ -841,7 +841,7 @@ __global__ __launch_bounds__(256, 1) void k_online_persist(PersistArgs a) {
     uint32_t first = 0;
     for (int l = 0; l < a.n; l++) {
         const LayerDev &L = a.Ls[l];
-        const uint32_t tiles = L.fo ? (uint32_t)(((L.N + 63) / 64) * ((L.K + 31) / 32)) : 0;
+        const uint32_t tiles = L.fo == FO_DIGITS ? (uint32_t)(((L.N + 63) / 64) * ((L.K + 31) / 32)) : 0;
         for (uint32_t t = (w + W - first % W) % W; t < tiles; t += W) open_pack_body<R>(a.Ls, a.flags, Grid{t, (uint32_t)l, tiles});
         first += tiles;
     }

@@ -17,8 +17,18 @@
 
 #include "compacttag.h"
 #include "ct_internal.h"
+#include "ct_rns_plan.h"
 
 namespace ct {
+
+// Scratch of the residue products of a context or a plan: its lanes never use
+// it at once (the side lane runs between a fork from the main stream and the
+// join).  A context allocates it when it is created, a plan, if its layers take
+// that path, what they need of it.
+struct RnsMemory {
+    uint8_t *scratch = nullptr;
+    int64_t bytes = RNS_SCRATCH_BYTES;  // 0: could not be had
+};
 
 struct Lane {
     hipStream_t stream = nullptr;
@@ -27,9 +37,20 @@ struct Lane {
     GemmProb *gemm_dev = nullptr, *gemm_host = nullptr;
     PackJob *pack_dev = nullptr, *pack_host = nullptr;
     SkinnyProb *skinny_dev = nullptr, *skinny_host = nullptr;
+    // residue products: memory of the lane's context or plan (null: every product by digits; set before lane_init),
+    // and the lane's tables, one block on the device (rns_tables) and one pinned
+    RnsMemory *rns = nullptr;
+    uint8_t *rns_tables = nullptr, *rns_staging = nullptr;
+    RnsJob *rns_jobs_dev = nullptr, *rns_jobs_host = nullptr;     // max_jobs
+    RnsOpen *rns_open_dev = nullptr, *rns_open_host = nullptr;    // max_layers
+    RnsProb *rns_probs_dev = nullptr, *rns_probs_host = nullptr;  // max_probs
     u128 *acc_dev = nullptr;
     ct_check_result *res_dev = nullptr, *res_host = nullptr;
     uint32_t *sync_dev = nullptr;      // counters of the persistent launch (64 bytes)
+    // stream of another lane that is idle while this one runs (null: none): the residue products of one group of
+    // layers run there, beside the openings of the next
+    hipStream_t aux = nullptr;
+    hipEvent_t ev_ready = nullptr, ev_free[2] = {nullptr, nullptr}, ev_join = nullptr;
     hipEvent_t upload_done = nullptr;  // the staging copies may be rewritten once this has completed
     bool timed = false;                // per-launch event timing (the context's own lane only)
 };
@@ -46,7 +67,7 @@ enum Stage : int {
     ST_DEAL_LIFT, ST_FILL_ZERO, ST_DEAL_AUTH, ST_DEAL_SKINNY, ST_ZERO_ACC, ST_OPEN_U, ST_ROW_PASS, ST_PACK,
     ST_COPY_BASE, ST_RING_GEMM, ST_POST, ST_COMPACT_FINAL, ST_CHECK_BATCH, ST_CHECK_COMPACT, ST_FINALIZE,
     ST_COL_TAG, ST_CONV_COMPRESS, ST_NP_OPEN, ST_NP_SKINNY, ST_NP_COMPRESS, ST_NP_GEMV, ST_OPEN_PACK, ST_PERSIST,
-    ST_COUNT
+    ST_RNS_OPEN, ST_RNS_PACK, ST_RNS_GEMM, ST_RNS_FOLD, ST_COUNT
 };
 
 struct ct_ctx {
@@ -60,9 +81,10 @@ struct ct_ctx {
     // events that fork it from and join it to the main stream
     ct::Lane side;
     hipEvent_t fork = nullptr, join = nullptr;
-    bool overlap = true;  // mixed batches on two streams (ct_set_overlap)
+    bool overlap = true;  // mixed batches and groups of residue products on two streams (ct_set_overlap)
     int launch_mode = CT_LAUNCH_STAGED;  // ct_set_launch
     uint64_t launch_wait = CT_LAUNCH_WAIT_DEFAULT;  // ct_set_launch_wait
+    ct::RnsMemory rns;  // of both lanes
     std::string err;
     // per-launch timing: event pairs recorded around each kernel of the main lane
     bool timing = false;
@@ -104,6 +126,7 @@ struct OnlineLaunch {
     bool any_accum = false, compact = false, check = false, any_cm = false, any_conv_n = false;
     ct_mode mode = CT_MODE_COMPACT;
     GemmTuning tu;
+    RnsPlan rns;
     int64_t max_zero = 0, max_kn_items = 0, max_row_items = 0, max_mn = 0, max_mn_items = 0, max_col_tag = 0,
             max_conv_items = 0;
     // n-party path

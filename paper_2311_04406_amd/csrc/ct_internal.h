@@ -87,13 +87,16 @@ struct LayerDev {
     // share streams of parties 1 .. np - 2 (party 0 uses key[K_VSH_X + obj - 1] and
     // key[K_TSH_X + obj - 1]; the last party completes the sums)
     uint64_t vsh[MAXP - 2][NUM_OBJ], tsh[MAXP - 2][NUM_OBJ];
-    // two-party matrix-core layers that are not convolutions: U is opened by
+    // two-party matrix-core layers that are not convolutions: FO_DIGITS: U is opened by
     // k_open_pack, which also writes the digit tiles of [B]_0, [B]_1 and U
-    // (rp[0..2], in the workspace); k_open_u skips them
+    // (rp[0..2], in the workspace); FO_RNS: E and U are opened by the kernels
+    // that write the operands' residue planes.  k_open_u skips both
     int32_t fo;
     int32_t out_index;          // position of the layer's check record in the caller's result array
     u128 *rp[3];
 };
+
+enum Fo : int32_t { FO_NONE = 0, FO_DIGITS = 1, FO_RNS = 2 };
 
 // cvec offsets of n parties, compressing along N (see compacttag.h): U^c,
 // tB^c_p (K each), then D^c, E U^c, tC^c_p, tR^c_p, tZ^c_p, tD^c_p (M each).
@@ -156,7 +159,8 @@ constexpr int ACC_RP = 3 * ACC_W;
 constexpr int RP_CELLS = 1536;  // 64-bit cells (768 elements of 16 bytes)
 constexpr int RP_COPIES = RP_CELLS / 12;
 constexpr int NP_RP_COPIES = RP_CELLS / (4 * ACC_W);
-constexpr int ACC_PER_LAYER = 3 * ACC_W + RP_CELLS / 2;
+// k_rns_open_right adds its check sums of U into RP_COPIES more copies.
+constexpr int ACC_PER_LAYER = 3 * ACC_W + RP_CELLS;
 
 // cvec offsets (elements), see compacttag.h.  Compressing along M the same
 // offsets are taken with M replaced by N (cvec_off(N, K)), and the three
@@ -200,6 +204,8 @@ __host__ __device__ inline int cm_cw(int64_t N) {
 }
 // Bit of the row-pass variant set: 1 << v for k_row_pass<v>, 1 << (VARIANT_CM + v)
 // for k_row_pass_cm<v> (v = 0, 1, 2, 4, 8).
+// Bit VARIANT_E: k_row_pass_e, the pass of FO_RNS layers, which reads the opened E.
+constexpr int VARIANT_E = 9;
 constexpr int VARIANT_CM = 16;
 __host__ __device__ inline int64_t cm_strips(int64_t K, int cw) { return (K + 64 * cw - 1) / (64 * cw); }
 __host__ __device__ inline int64_t cm_items(int64_t M, int64_t K, int64_t N) {

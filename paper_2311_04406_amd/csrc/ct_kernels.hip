@@ -156,7 +156,7 @@ template <class R>
 __global__ __launch_bounds__(TPB) void k_open_u(const LayerDev *__restrict__ Ls, int flags) {
     __shared__ R sh[3 * WAVES];
     const LayerDev &L = Ls[blockIdx.y];
-    if (L.fo) return;  // opened by k_open_pack
+    if (L.fo != FO_NONE) return;  // opened by the kernels that convert the right operands
     const int64_t K = L.K, N = L.N;
     // a layer compressed along M has no K-long compressions of U and [tB]_p
     const bool check = flags & F_CHECK, compact = (flags & F_COMPACT) && !L.cm;
@@ -403,9 +403,21 @@ __device__ __forceinline__ void row_pass_cm(const LayerDev &L, int flags, R (&ch
 template <class R, int NS>
 __global__ __launch_bounds__(TPB) void k_row_pass(const LayerDev *__restrict__ Ls, int flags) {
     const LayerDev &L = Ls[blockIdx.y];
-    if (row_variant(L.N) != NS || ((flags & F_COMPACT) && L.cm)) return;
+    if (row_variant(L.N) != NS || ((flags & F_COMPACT) && L.cm) || L.fo == FO_RNS) return;
     R chk[3] = {Ring<R>::zero(), Ring<R>::zero(), Ring<R>::zero()};
     row_pass_body<R, NS>(L, flags, chk, hw_grid());
+    if (flags & F_CHECK)
+        wave_accumulate_limbs<3>(chk, rp_cells<R>(L) + 12 * (((blockIdx.x * TPB + threadIdx.x) >> 6) % RP_COPIES));
+}
+
+// The pass of FO_RNS layers, whose E k_rns_open_left opened (80 bytes an
+// element are left to read: E and the four tag shares).
+template <class R>
+__global__ __launch_bounds__(TPB) void k_row_pass_e(const LayerDev *__restrict__ Ls, int flags) {
+    const LayerDev &L = Ls[blockIdx.y];
+    if (L.fo != FO_RNS) return;
+    R chk[3] = {Ring<R>::zero(), Ring<R>::zero(), Ring<R>::zero()};
+    row_pass_body<R, 0, true>(L, flags, chk, hw_grid());
     if (flags & F_CHECK)
         wave_accumulate_limbs<3>(chk, rp_cells<R>(L) + 12 * (((blockIdx.x * TPB + threadIdx.x) >> 6) % RP_COPIES));
 }
@@ -432,6 +444,7 @@ void launch_row_variants(const dim3 &g, const LayerDev *L, int flags, int varian
     if (variants & (1 << 2)) hipLaunchKernelGGL((k_row_pass<R, 2>), g, b, 0, st, L, flags);
     if (variants & (1 << 4)) hipLaunchKernelGGL((k_row_pass<R, 4>), g, b, 0, st, L, flags);
     if (variants & (1 << 8)) hipLaunchKernelGGL((k_row_pass<R, SKINNY_MAX_N>), g, b, 0, st, L, flags);
+    if (variants & (1 << VARIANT_E)) hipLaunchKernelGGL((k_row_pass_e<R>), g, b, 0, st, L, flags);
     if (variants & (1 << (VARIANT_CM + 0))) hipLaunchKernelGGL((k_row_pass_cm<R, 0>), g, b, 0, st, L, flags);
     if (variants & (1 << (VARIANT_CM + 1))) hipLaunchKernelGGL((k_row_pass_cm<R, 1>), g, b, 0, st, L, flags);
     if (variants & (1 << (VARIANT_CM + 2))) hipLaunchKernelGGL((k_row_pass_cm<R, 2>), g, b, 0, st, L, flags);

@@ -52,7 +52,9 @@ __device__ __forceinline__ void prob_base_body(const GemmProb *__restrict__ prob
 
 // The pass over M x K of a layer that is not compressed along M: one
 // wavefront per row segment of row_seg(M, K) elements (see ct_kernels.hip).
-template <class R, int NS>
+// FE: E was opened before (FO_RNS layers) and is read instead of the shares
+// of X and A; there is no folded operand to write.
+template <class R, int NS, bool FE = false>
 __device__ __forceinline__ void row_pass_body(const LayerDev &L, int flags, R (&chk)[3], const Grid &g) {
     const int lane = threadIdx.x & 63;
     const int64_t M = L.M, K = L.K, N = L.N;
@@ -87,10 +89,14 @@ __device__ __forceinline__ void row_pass_body(const LayerDev &L, int flags, R (&
         auto load = [&](int64_t e, In &v) {
             // the arrays are streamed, except [A]_1 of a matrix-core layer,
             // which k_pack reads next
-            v.a0 = ld_nt(P<R>(L.A[0]), e);
-            v.a1 = skinny ? ld_nt(P<R>(L.A[1]), e) : ld(P<R>(L.A[1]), e);
-            v.x0 = ld_nt(P<R>(L.X[0]), e);
-            v.x1 = ld_nt(P<R>(L.X[1]), e);
+            if constexpr (FE) {
+                v.x0 = ld_nt(P<R>(L.E), e);
+            } else {
+                v.a0 = ld_nt(P<R>(L.A[0]), e);
+                v.a1 = skinny ? ld_nt(P<R>(L.A[1]), e) : ld(P<R>(L.A[1]), e);
+                v.x0 = ld_nt(P<R>(L.X[0]), e);
+                v.x1 = ld_nt(P<R>(L.X[1]), e);
+            }
             v.ta0 = v.ta1 = v.tx0 = v.tx1 = Ring<R>::zero();
             if (need_ta) {
                 v.ta0 = ld_nt(P<R>(L.tA[0]), e);
@@ -103,11 +109,13 @@ __device__ __forceinline__ void row_pass_body(const LayerDev &L, int flags, R (&
         };
         auto use = [&](int64_t k, const In &v) {
             const int64_t e = rb + k;
-            const R E = add(sub(v.x0, v.a0), sub(v.x1, v.a1));
+            const R E = FE ? v.x0 : add(sub(v.x0, v.a0), sub(v.x1, v.a1));
             // E of a layer whose products are formed here is not read again
             // in the step; a matrix-core layer's is packed next
-            if (skinny) st_nt(P<R>(L.E), e, E);
-            else st(P<R>(L.E), e, E);
+            if constexpr (!FE) {
+                if (skinny) st_nt(P<R>(L.E), e, E);
+                else st(P<R>(L.E), e, E);
+            }
             if (check) {
                 const uint64_t x = Ring<R>::mod_s(sdraw(kce, (uint64_t)e));
                 chk[0] = mad64(chk[0], sub(v.tx0, v.ta0), x);
@@ -122,7 +130,8 @@ __device__ __forceinline__ void row_pass_body(const LayerDev &L, int flags, R (&
                 cp[3] = mad(cp[3], v.ta0, uc);
                 cp[4] = mad(cp[4], v.ta1, uc);
             }
-            if constexpr (!skinny) {
+            if constexpr (FE) {
+            } else if constexpr (!skinny) {
                 // folded left operands of the matrix-core products:
                 //   [Z]_0 = [C]_0 + E [B]_0 + (A_0 + E) U,
                 //   [tZ]_p = [tC]_p + E [tB]_p + ([tA]_p + [Delta]_p E) U
@@ -335,17 +344,37 @@ __device__ __forceinline__ void finalize_body(const LayerDev *__restrict__ Ls, i
         }
         e[i] = wave_sum(e[i]);
     }
+    // and k_rns_open_right's copies of the U sums
+    R u[3];
+    if constexpr (sizeof(R) == 16) {
+        const unsigned long long *uc = u_cells(L);
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            u[i] = Ring<R>::zero();
+            if (L.fo == FO_RNS) {
+                for (int s = lane; s < RP_COPIES; s += 64) {
+                    R v;
+                    from_limbs(uc + 12 * s + 4 * i, v);
+                    u[i] = add(u[i], v);
+                }
+                u[i] = wave_sum(u[i]);
+            }
+        }
+    } else {
+        u[0] = u[1] = u[2] = Ring<R>::zero();
+    }
     if (lane != 0) return;
     for (int i = 0; i < 3; i++) e[i] = add(e[i], ld(P<R>(L.acc), i));
+    for (int i = 0; i < 3; i++) u[i] = add(u[i], ld(P<R>(L.acc), 3 + i));
     int ok = 1;
     ct_check_result r;
     for (int w = 0; w < 3; w++)
         for (int p = 0; p < CT_MAX_PARTIES; p++) r.cs[w][p] = ct_u128{0, 0};
     for (int w = 0; w < 3; w++) {
-        const R aw = w == 0 ? e[2] : ld(P<R>(L.acc), 3 * w + 2);
+        const R aw = w == 0 ? e[2] : w == 1 ? u[2] : ld(P<R>(L.acc), 3 * w + 2);
         R c[2];
         for (int p = 0; p < 2; p++) {
-            c[p] = sub(w == 0 ? e[p] : ld(P<R>(L.acc), 3 * w + p), mul64(aw, L.delta[p]));
+            c[p] = sub(w == 0 ? e[p] : w == 1 ? u[p] : ld(P<R>(L.acc), 3 * w + p), mul64(aw, L.delta[p]));
             r.cs[w][p] = Ring<R>::out(c[p]);
         }
         if (Ring<R>::nonzero(add(c[0], c[1]))) ok = 0;

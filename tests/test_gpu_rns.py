@@ -1,0 +1,89 @@
+"""Products through residues (k = s = 64) against the oracle, bit-exact, at the
+edges of their tiles and chunks, and on operands at the ends of their range
+against the closed form.  Every case checks that the residue path ran."""
+import pytest
+import torch
+
+import oracle as O
+from gpu_util import compare_cs, compare_layer, free, gpu_layers, oracle_run, say
+from paper_2311_04406_amd.binding import RESULT_WORDS
+
+pytestmark = pytest.mark.gpu
+KEY = 11
+
+
+class Spec:
+    def __init__(self, M, K, N, f=0, compress=0, conv=None):
+        self.M, self.K, self.N, self.seed, self.layer_id = M, K, N, 91, 4
+        self.f, self.compress, self.conv = f, compress, conv
+        self.name = f"{M}x{K}x{N}"
+
+
+def staged_run(ctx, mode, layers, out):
+    """One fused call with stage timing; returns the stages that ran."""
+    ctx.set_timing(True)
+    ctx.stage_times()
+    ctx.tag_linear_check(mode, layers, out)
+    torch.cuda.synchronize()
+    st = ctx.stage_times()
+    ctx.set_timing(False)
+    return st
+
+
+# M, N: one past, one short of and at multiples of 32-row blocks and 128-row
+# tiles; K: ragged slices of 64, one to several chunks
+CASES = [(Spec(449, 705, 481), 2, 1), (Spec(512, 640, 512), 2, 1), (Spec(415, 1100, 415), 2, 0),
+         (Spec(545, 1100, 513, f=13, compress=1), 2, 1), (Spec(481, 897, 484, conv=(897, 22, 22, 1, 1, 0)), 2, 1),
+         (Spec(385, 1152, 784, conv=(128, 28, 28, 3, 1, 1)), 2, 1),
+         (Spec(417, 1100, 450), 3, 1), (Spec(353, 900, 448), 4, 0), (Spec(481, 700, 450), 5, 1)]
+
+
+@pytest.mark.parametrize("spec,parties,mode", CASES, ids=[f"{s.name}-p{p}-m{m}" for s, p, m in CASES])
+def test_residue_products_bit_exact(spec, parties, mode):
+    from paper_2311_04406_amd import Context
+    ctx = Context(device=0, key_seed=KEY, parties=parties)
+    layers = gpu_layers(ctx, [spec])
+    layers[0]["work"].fill_(0x5A5A5A5A5A5A5A5A)   # the workspace's contents are undefined before a call
+    ctx.gen_triple_tags(layers)
+    out = torch.zeros(RESULT_WORDS, dtype=torch.int64, device="cuda:0")
+    say(f"[rns] {spec.name} p={parties} mode={mode}")
+    st = staged_run(ctx, mode, layers, out)
+    assert "rns_gemm" in st, st
+    ol = oracle_run(mode, spec, KEY, parties=parties)
+    compare_layer(layers[0], ol, mode, dealt=False, what=spec.name)
+    res = Context.decode_results(out, 1, parties)[0]
+    compare_cs(res, ol, what=spec.name)
+    assert res.accept
+    ctx.close()
+    free()
+
+
+def fill(t, v):
+    """Every element of a ring tensor = v mod 2^128."""
+    for i in range(2):
+        w = (v >> (64 * i)) & ((1 << 64) - 1)
+        t[..., i] = w - (1 << 64) if w >> 63 else w
+
+
+@pytest.mark.parametrize("K", [1024, 4700])   # 4700: near the largest sum the residue system holds
+@pytest.mark.parametrize("e,b,u", [(-1 << 127, -1 << 127, -1 << 127), (-1 << 127, (1 << 127) - 1, (1 << 127) - 1),
+                                   ((1 << 127) - 1, (1 << 127) - 1, (1 << 127) - 1), (1, -1 << 127, 0), (0, 0, 0)])
+def test_operands_at_the_ends_of_their_range(K, e, b, u):
+    """E, [B]_p, U, A_0 + E and [A]_1 all at one end: the sums reach the bound."""
+    from paper_2311_04406_amd import Context
+    M, N = 450, 420
+    ctx = Context(device=0, key_seed=KEY)
+    L = ctx.layer(M, K, N, 5, 6)
+    a1, mod = e, 1 << 128
+    for p, (x, a, y, bb) in enumerate([(e, 0, u + b, b), (a1, a1, b, b)]):
+        for n, v in (("X", x), ("A", a), ("Y", y), ("B", bb), ("C", 3 + p)):
+            fill(L[n][p], v)
+    out = torch.zeros(RESULT_WORDS, dtype=torch.int64, device="cuda:0")
+    say(f"[rns] K={K} e={e} b={b} u={u}")
+    assert "rns_gemm" in staged_run(ctx, O.MODE_COMPACT, [L], out)
+    for p, z in enumerate([3 + K * (e * b + e * u), 4 + K * (e * b + a1 * u)]):
+        want = torch.zeros_like(L["Z"][p])
+        fill(want, z % mod)
+        assert torch.equal(L["Z"][p], want), (p, L["Z"][p][0, 0].tolist(), want[0, 0].tolist())
+    ctx.close()
+    free()
