@@ -243,6 +243,10 @@ void fill_layer(const ct_ctx *c, u128 *acc, const ct_layer_desc &d, const ct_lay
         o.cv.wo = (d.conv_w + 2 * d.conv_pad - d.conv_k) / d.conv_stride + 1;
     }
     o.nr = CT_RIGHT_LEN(d);
+    o.row_seg = (int32_t)row_seg(d.M, d.K);
+    o.row_segs = (int32_t)((d.K + o.row_seg - 1) / o.row_seg);
+    o.cm_rows = (int32_t)cm_rb(d.M, d.K, d.N);
+    o.cm_items = (int32_t)cm_items(d.M, d.K, d.N);
     o.E = reinterpret_cast<u128 *>(b.E);
     o.U = reinterpret_cast<u128 *>(b.U);
     o.D = reinterpret_cast<u128 *>(b.D);

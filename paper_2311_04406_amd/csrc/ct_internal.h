@@ -93,6 +93,9 @@ struct LayerDev {
     // that write the operands' residue planes.  k_open_u skips both
     int32_t fo;
     int32_t out_index;          // position of the layer's check record in the caller's result array
+    int32_t row_seg, row_segs;  // row pass: elements of an item, items per row (row_seg below)
+    int32_t cm_rows;            // the same compressing along M: rows of an item (cm_rb below)
+    int32_t cm_items;           // and the number of items
     u128 *rp[3];
 };
 
@@ -120,19 +123,25 @@ __host__ __device__ inline NpCvec np_cvec(int64_t M, int64_t K, int np) {
 // the pass that opens E (no MFMA tiles, no workspace).
 constexpr int SKINNY_MAX_N = 8;
 
-// Elements of one row of E per work item of the row pass (a multiple of 64,
-// at least 1024): long rows are cut into several items, so that a layer
-// with few rows still spreads over the whole GPU; segments double while the
-// layer keeps at least 16384 items.  Each item ends in wavefront reductions
-// and atomic additions of its row products, so short items cost: on the
-// batched set (K from 32 to 4096) the pass took 1.22 ms with items of at
-// least 256 elements, 0.87 ms with 512 and 0.77 ms with 1024.
-__host__ __device__ inline int64_t row_seg(int64_t M, int64_t K) {
+// Elements of one row of E per work item of the row pass (a multiple of 64):
+// long rows are cut into several items, so that a layer with few rows still
+// spreads over the whole GPU; segments double while the layer keeps at least
+// 16384 items.  Each item ends in wavefront reductions and atomic additions of
+// its row products, so short items cost: on the batched set (K from 32 to
+// 4096) the pass took 1.22 ms with items of at least 256 elements, 0.87 ms
+// with 512 and 0.77 ms with 1024.  A layer with fewer than ROW_ITEMS items of
+// 1024 (two wavefronts a compute unit) is bound by the chain of an item's
+// iterations, about 2 us each, and is cut shorter, down to two iterations: the
+// pass took 28 us instead of 39 on an encoder's layers, 0.58 ms instead of
+// 0.75 on 64 uneven ones; with four times as many items 0.75, with half 0.58.
+constexpr int64_t ROW_ITEMS = 512, ROW_SEG_MIN = 128;
+inline int64_t row_seg(int64_t M, int64_t K) {
     int64_t s = 1024;
     while (s < 4096 && M * ((K + 2 * s - 1) / (2 * s)) >= 16384) s *= 2;
+    while (s > ROW_SEG_MIN && M * ((K + s - 1) / s) < ROW_ITEMS) s /= 2;
     return s;
 }
-__host__ __device__ inline int64_t row_items(int64_t M, int64_t K) {
+inline int64_t row_items(int64_t M, int64_t K) {
     const int64_t s = row_seg(M, K);
     return M * ((K + s - 1) / s);
 }
@@ -194,10 +203,16 @@ __host__ __device__ inline int row_variant(int64_t N) {
 __host__ __device__ inline bool np_fused_row(int64_t N) { return N > SKINNY_MAX_N || N <= 2; }
 
 // Row pass of a layer compressed along M: lanes own columns; a wavefront
-// takes a strip of cm_cw(N) * 64 columns over CM_RB rows and keeps the column
-// sums chi_m E_mk, chi_m [tA]_p,mk in registers until its rows are done
+// takes a strip of cm_cw(N) * 64 columns over cm_rb(M, K, N) rows and keeps the
+// column sums chi_m E_mk, chi_m [tA]_p,mk in registers until its rows are done
 // (narrower strips for skinny layers, whose row products take registers too).
+// At most CM_RB rows, fewer while the layer has less than CM_ITEMS items: its
+// rows come one after another, a few us each, while an item's end costs three
+// atomic additions per column.  512 x 4608 x 49 took 167 us with 32 rows, 102
+// with 8 (1152 items), 110 with 4 and 137 with 2 (its 377 MB take 80);
+// 64 x 1000 x 3 took 182 us with 32 rows, about 30 with 2.
 constexpr int CM_RB = 32;
+constexpr int64_t CM_ITEMS = 1024, CM_RB_MIN = 2;
 __host__ __device__ constexpr int cm_cw_variant(int ns) { return ns == 0 || ns == 1 ? 4 : (ns == 2 ? 2 : 1); }
 __host__ __device__ inline int cm_cw(int64_t N) {
     return cm_cw_variant(N > 8 ? 0 : (N <= 1 ? 1 : (N <= 2 ? 2 : (N <= 4 ? 4 : 8))));
@@ -208,8 +223,15 @@ __host__ __device__ inline int cm_cw(int64_t N) {
 constexpr int VARIANT_E = 9;
 constexpr int VARIANT_CM = 16;
 __host__ __device__ inline int64_t cm_strips(int64_t K, int cw) { return (K + 64 * cw - 1) / (64 * cw); }
-__host__ __device__ inline int64_t cm_items(int64_t M, int64_t K, int64_t N) {
-    return cm_strips(K, cm_cw(N)) * ((M + CM_RB - 1) / CM_RB);
+inline int64_t cm_rb(int64_t M, int64_t K, int64_t N) {
+    const int64_t strips = cm_strips(K, cm_cw(N));
+    int64_t rb = CM_RB;
+    while (rb > CM_RB_MIN && strips * ((M + rb - 1) / rb) < CM_ITEMS) rb /= 2;
+    return rb;
+}
+inline int64_t cm_items(int64_t M, int64_t K, int64_t N) {
+    const int64_t rb = cm_rb(M, K, N);
+    return cm_strips(K, cm_cw(N)) * ((M + rb - 1) / rb);
 }
 
 // Column sweep (sums down the columns of a rows x N matrix): wavefront items

@@ -282,7 +282,7 @@ hipError_t launch_open_u(int eb, const LayerDev *L, int n, int flags, int64_t ma
 // besides opening E, checking it and (N <= SKINNY_MAX_N) forming the output
 // products, it compresses E and [tA]_p down the columns,
 //   E^c_k = sum_m chi_m E_mk,  [tA^c]_p,k = sum_m chi_m [tA]_p,mk  (Fig. 4 along M).
-// Work items are strips of cm_cw(N) * 64 columns over CM_RB rows, ordered
+// Work items are strips of cm_cw(N) * 64 columns over cm_rb(M, K, N) rows, ordered
 // row-block-major so that concurrent wavefronts read neighbouring columns of
 // the same rows and add their column sums to different addresses.
 template <class R, int NS>
@@ -294,7 +294,7 @@ __device__ __forceinline__ void row_pass_cm(const LayerDev &L, int flags, R (&ch
     const uint64_t kce = L.key[K_CHI_E], kchi = L.key[K_CHI];
     R *AE0 = P<R>(L.work);
     constexpr int CM_CW = cm_cw_variant(NS);
-    const int64_t strips = cm_strips(K, CM_CW), items = cm_items(M, K, N);
+    const int64_t strips = cm_strips(K, CM_CW), rows = L.cm_rows, items = L.cm_items;
     // output products of the item's rows (N <= SKINNY_MAX_N), per wavefront:
     // added at the end of the item, all rows' atomics in flight together
     constexpr int NSX = NS > 0 ? NS : 1;
@@ -305,7 +305,7 @@ __device__ __forceinline__ void row_pass_cm(const LayerDev &L, int flags, R (&ch
     const int64_t nwaves = ((int64_t)gridDim.x * TPB) >> 6;
     for (int64_t it = wave_id; it < items; it += nwaves) {
         const int64_t rb = it / strips, sg = it - rb * strips;
-        const int64_t m0 = rb * CM_RB, m1 = m0 + CM_RB < M ? m0 + CM_RB : M;
+        const int64_t m0 = rb * rows, m1 = m0 + rows < M ? m0 + rows : M;
         const int64_t kb = sg * (64 * CM_CW) + lane;
         R ce[CM_CW], ca0[CM_CW], ca1[CM_CW];
 #pragma unroll

@@ -270,7 +270,7 @@ __global__ __launch_bounds__(TPB) void k_np_row_pass(const LayerDev *__restrict_
     R chk[ACC_W];
 #pragma unroll
     for (int i = 0; i < ACC_W; i++) chk[i] = Ring<R>::zero();
-    const int64_t seg = row_seg(M, K), items = M * ((K + seg - 1) / seg);
+    const int64_t seg = L.row_seg, items = M * L.row_segs;
     const int64_t wave_id = (blockIdx.x * (int64_t)TPB + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)gridDim.x * TPB) >> 6;
     for (int64_t it = wave_id; it < items; it += nwaves) {

@@ -65,7 +65,7 @@ __device__ __forceinline__ void row_pass_body(const LayerDev &L, int flags, R (&
     const uint64_t kce = L.key[K_CHI_E];
     const uint64_t d0 = L.delta[0], d1 = L.delta[1];
     R *AE0 = P<R>(L.work), *tAE0 = P<R>(L.work) + M * K, *tAE1 = P<R>(L.work) + 2 * M * K;
-    const int64_t seg = row_seg(M, K), items = M * ((K + seg - 1) / seg);
+    const int64_t seg = L.row_seg, items = M * L.row_segs;
     const int64_t wave_id = ((int64_t)g.x * TPB + threadIdx.x) >> 6;
     const int64_t nwaves = ((int64_t)g.nx * TPB) >> 6;
     // segment-major order: the wavefronts in flight share one segment of k,
