@@ -296,12 +296,39 @@ Sizes max_sizes(const ct_layer_desc *L, int n) {
     return s;
 }
 
+// Lays out the tables of a call of n layers from the start of the lane's
+// blocks; returns their end.  (Launches in flight may still read the previous
+// call's: the stream orders the upload after them.)
+int64_t lane_place(Lane &ln, int n, int np) {
+    // up to two products per party and 4 np + 2 packed operands per layer
+    ln.max_probs = 2 * np * n;
+    ln.max_jobs = (4 * np + 2) * n;
+    int64_t at = 0;
+    auto place = [&](auto *&dev, auto *&host, int count) {
+        using T = std::remove_reference_t<decltype(*host)>;
+        dev = reinterpret_cast<T *>(ln.dev + at);
+        host = reinterpret_cast<T *>(ln.host + at);
+        at = (at + (int64_t)sizeof(T) * count + 255) & ~(int64_t)255;
+    };
+    place(ln.layers_dev, ln.layers_host, n);
+    place(ln.gemm_dev, ln.gemm_host, ln.max_probs);
+    place(ln.pack_dev, ln.pack_host, ln.max_jobs);
+    place(ln.skinny_dev, ln.skinny_host, n);
+    if (ln.rns) {
+        place(ln.rns_open_dev, ln.rns_open_host, n);
+        place(ln.rns_probs_dev, ln.rns_probs_host, ln.max_probs);
+        place(ln.rns_jobs_dev, ln.rns_jobs_host, ln.max_jobs);
+    }
+    return at;
+}
+
 // Waits for the lane's previous upload, then stages the layer records.
 // out_index: position of each layer's check record in the caller's result
 // array (null: the layer's own position).
 ct_status stage_layers(ct_ctx *c, Lane &ln, const ct_layer_desc *L, const ct_layer_bufs *B, int n,
                        const int *out_index = nullptr) {
     HIPCHK(c, hipEventSynchronize(ln.upload_done));
+    lane_place(ln, n, c->np);
     for (int l = 0; l < n; l++) {
         fill_layer(c, ln.acc_dev, L[l], B[l], l, ln.layers_host[l]);
         ln.layers_host[l].out_index = out_index ? out_index[l] : l;
@@ -309,28 +336,22 @@ ct_status stage_layers(ct_ctx *c, Lane &ln, const ct_layer_desc *L, const ct_lay
     return CT_OK;
 }
 
+// One copy, up to the end of the last table in use: on the device it is a
+// kernel of 3 to 5 us whatever its size (6 KB a layer), and the small layers'
+// calls had three of them.
 ct_status upload(ct_ctx *c, Lane &ln, int n, int nprobs, int njobs = 0, int nskinny = 0,
                  const RnsPlan &rns = RnsPlan()) {
-    if (rns.nprobs > 0) {
-        HIPCHK(c, hipMemcpyAsync(ln.rns_probs_dev, ln.rns_probs_host, sizeof(RnsProb) * rns.nprobs,
-                                 hipMemcpyHostToDevice, ln.stream));
-        if (rns.njobs > 0)
-            HIPCHK(c, hipMemcpyAsync(ln.rns_jobs_dev, ln.rns_jobs_host, sizeof(RnsJob) * rns.njobs,
-                                     hipMemcpyHostToDevice, ln.stream));
-        if (rns.nopen > 0)
-            HIPCHK(c, hipMemcpyAsync(ln.rns_open_dev, ln.rns_open_host, sizeof(RnsOpen) * rns.nopen,
-                                     hipMemcpyHostToDevice, ln.stream));
-    }
-    HIPCHK(c, hipMemcpyAsync(ln.layers_dev, ln.layers_host, sizeof(LayerDev) * n, hipMemcpyHostToDevice, ln.stream));
-    if (nprobs > 0)
-        HIPCHK(c, hipMemcpyAsync(ln.gemm_dev, ln.gemm_host, sizeof(GemmProb) * nprobs, hipMemcpyHostToDevice,
-                                 ln.stream));
-    if (njobs > 0)
-        HIPCHK(c, hipMemcpyAsync(ln.pack_dev, ln.pack_host, sizeof(PackJob) * njobs, hipMemcpyHostToDevice,
-                                 ln.stream));
-    if (nskinny > 0)
-        HIPCHK(c, hipMemcpyAsync(ln.skinny_dev, ln.skinny_host, sizeof(SkinnyProb) * nskinny,
-                                 hipMemcpyHostToDevice, ln.stream));
+    const uint8_t *end = reinterpret_cast<const uint8_t *>(ln.layers_host + n);
+    auto upto = [&](const void *p, int count) {
+        if (count > 0) end = std::max(end, static_cast<const uint8_t *>(p));
+    };
+    upto(ln.gemm_host + nprobs, nprobs);
+    upto(ln.pack_host + njobs, njobs);
+    upto(ln.skinny_host + nskinny, nskinny);
+    upto(ln.rns_open_host + rns.nopen, rns.nopen);
+    upto(ln.rns_probs_host + rns.nprobs, rns.nprobs);
+    upto(ln.rns_jobs_host + rns.njobs, rns.njobs);
+    HIPCHK(c, hipMemcpyAsync(ln.dev, ln.host, end - ln.host, hipMemcpyHostToDevice, ln.stream));
     HIPCHK(c, hipEventRecord(ln.upload_done, ln.stream));
     return CT_OK;
 }
@@ -635,39 +656,22 @@ ct_status fail(ct_ctx *c, ct_status s, const std::string &msg) {
     return s;
 }
 
-hipError_t lane_init(Lane &ln, hipStream_t stream, int max_layers) {
+hipError_t lane_init(Lane &ln, hipStream_t stream, int max_layers, int np) {
     ln.stream = stream;
     ln.max_layers = max_layers;
-    // up to two products per party and 4 n + 2 packed operands per layer
-    ln.max_probs = 2 * CT_MAX_PARTIES * max_layers;
-    ln.max_jobs = (4 * CT_MAX_PARTIES + 2) * max_layers;
     hipError_t err;
 #define LANE_TRY(expr) \
     if ((err = (expr)) != hipSuccess) return err
-    LANE_TRY(hipMalloc(&ln.layers_dev, sizeof(LayerDev) * ln.max_layers));
-    LANE_TRY(hipMalloc(&ln.gemm_dev, sizeof(GemmProb) * ln.max_probs));
-    LANE_TRY(hipMalloc(&ln.pack_dev, sizeof(PackJob) * ln.max_jobs));
-    LANE_TRY(hipMalloc(&ln.skinny_dev, sizeof(SkinnyProb) * ln.max_layers));
-    LANE_TRY(hipMalloc(&ln.acc_dev, sizeof(u128) * ACC_PER_LAYER * ln.max_layers));
-    LANE_TRY(hipMalloc(&ln.res_dev, sizeof(ct_check_result) * ln.max_layers));
-    LANE_TRY(hipMalloc(&ln.sync_dev, 64));
-    LANE_TRY(hipHostMalloc(&ln.layers_host, sizeof(LayerDev) * ln.max_layers, hipHostMallocDefault));
-    LANE_TRY(hipHostMalloc(&ln.gemm_host, sizeof(GemmProb) * ln.max_probs, hipHostMallocDefault));
-    LANE_TRY(hipHostMalloc(&ln.pack_host, sizeof(PackJob) * ln.max_jobs, hipHostMallocDefault));
-    LANE_TRY(hipHostMalloc(&ln.skinny_host, sizeof(SkinnyProb) * ln.max_layers, hipHostMallocDefault));
-    LANE_TRY(hipHostMalloc(&ln.res_host, sizeof(ct_check_result) * ln.max_layers, hipHostMallocDefault));
-    if (ln.rns) {
-        const int64_t open = rns_align(sizeof(RnsOpen) * ln.max_layers), jobs = rns_align(sizeof(RnsJob) * ln.max_jobs),
-                      probs = rns_align(sizeof(RnsProb) * ln.max_probs);
-        LANE_TRY(hipMalloc(&ln.rns_tables, open + jobs + probs));
-        LANE_TRY(hipHostMalloc(&ln.rns_staging, open + jobs + probs, hipHostMallocDefault));
-        ln.rns_open_dev = reinterpret_cast<RnsOpen *>(ln.rns_tables);
-        ln.rns_jobs_dev = reinterpret_cast<RnsJob *>(ln.rns_tables + open);
-        ln.rns_probs_dev = reinterpret_cast<RnsProb *>(ln.rns_tables + open + jobs);
-        ln.rns_open_host = reinterpret_cast<RnsOpen *>(ln.rns_staging);
-        ln.rns_jobs_host = reinterpret_cast<RnsJob *>(ln.rns_staging + open);
-        ln.rns_probs_host = reinterpret_cast<RnsProb *>(ln.rns_staging + open + jobs);
-    }
+    const int64_t tables = lane_place(ln, max_layers, np);  // sizes only: the blocks do not exist yet
+    const int64_t acc = sizeof(u128) * ACC_PER_LAYER * (int64_t)max_layers;
+    const int64_t res = (sizeof(ct_check_result) * (int64_t)max_layers + 255) & ~(int64_t)255;
+    LANE_TRY(hipMalloc(&ln.dev, tables + acc + res + 64));
+    LANE_TRY(hipHostMalloc(&ln.host, tables + res, hipHostMallocDefault));
+    lane_place(ln, max_layers, np);
+    ln.acc_dev = reinterpret_cast<u128 *>(ln.dev + tables);
+    ln.res_dev = reinterpret_cast<ct_check_result *>(ln.dev + tables + acc);
+    ln.sync_dev = reinterpret_cast<uint32_t *>(ln.dev + tables + acc + res);
+    ln.res_host = reinterpret_cast<ct_check_result *>(ln.host + tables);
     LANE_TRY(hipEventCreateWithFlags(&ln.upload_done, hipEventDisableTiming));
     LANE_TRY(hipEventRecord(ln.upload_done, ln.stream));
     for (hipEvent_t *e : {&ln.ev_ready, &ln.ev_free[0], &ln.ev_free[1], &ln.ev_join})
@@ -677,23 +681,10 @@ hipError_t lane_init(Lane &ln, hipStream_t stream, int max_layers) {
 }
 
 void lane_free(Lane &ln) {
-    if (ln.upload_done) (void)hipEventDestroy(ln.upload_done);
-    for (hipEvent_t e : {ln.ev_ready, ln.ev_free[0], ln.ev_free[1], ln.ev_join})
+    for (hipEvent_t e : {ln.upload_done, ln.ev_ready, ln.ev_free[0], ln.ev_free[1], ln.ev_join})
         if (e) (void)hipEventDestroy(e);
-    if (ln.rns_tables) (void)hipFree(ln.rns_tables);
-    if (ln.rns_staging) (void)hipHostFree(ln.rns_staging);
-    if (ln.sync_dev) (void)hipFree(ln.sync_dev);
-    if (ln.layers_dev) (void)hipFree(ln.layers_dev);
-    if (ln.gemm_dev) (void)hipFree(ln.gemm_dev);
-    if (ln.pack_dev) (void)hipFree(ln.pack_dev);
-    if (ln.skinny_dev) (void)hipFree(ln.skinny_dev);
-    if (ln.acc_dev) (void)hipFree(ln.acc_dev);
-    if (ln.res_dev) (void)hipFree(ln.res_dev);
-    if (ln.layers_host) (void)hipHostFree(ln.layers_host);
-    if (ln.gemm_host) (void)hipHostFree(ln.gemm_host);
-    if (ln.pack_host) (void)hipHostFree(ln.pack_host);
-    if (ln.skinny_host) (void)hipHostFree(ln.skinny_host);
-    if (ln.res_host) (void)hipHostFree(ln.res_host);
+    if (ln.dev) (void)hipFree(ln.dev);
+    if (ln.host) (void)hipHostFree(ln.host);
     ln = Lane();
 }
 
@@ -725,10 +716,10 @@ ct_status ct_create(ct_ctx **out, const ct_params *p) {
             c->num_cus = cus;
         const int ml = p->max_layers > 0 ? p->max_layers : 256;
         if (c->eb == 16 && rns_alloc(c->rns)) c->main.rns = c->side.rns = &c->rns;
-        e = lane_init(c->main, reinterpret_cast<hipStream_t>(p->hip_stream), ml);
+        e = lane_init(c->main, reinterpret_cast<hipStream_t>(p->hip_stream), ml, c->np);
         hipStream_t side = nullptr;
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
-        if (e == hipSuccess) e = lane_init(c->side, side, ml);
+        if (e == hipSuccess) e = lane_init(c->side, side, ml, c->np);
         else c->side.stream = side;
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->fork, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&c->join, hipEventDisableTiming);
@@ -748,7 +739,7 @@ ct_status ct_create(ct_ctx **out, const ct_params *p) {
 
 ct_status ct_destroy(ct_ctx *c) {
     if (!c) return CT_EINVAL;
-    if (c->main.layers_dev) (void)hipStreamSynchronize(c->main.stream);
+    if (c->main.dev) (void)hipStreamSynchronize(c->main.stream);
     if (c->side.stream) (void)hipStreamSynchronize(c->side.stream);
     for (auto e : c->ev_start) (void)hipEventDestroy(e);
     for (auto e : c->ev_end) (void)hipEventDestroy(e);
@@ -1201,7 +1192,7 @@ ct_status prepare_online_split(ct_ctx *c, Lane &a, Lane &b, ct_mode mode, const 
                                OnlineLaunch &Pb, bool &split) {
     split = false;
     if (!c) return CT_EINVAL;
-    if (n <= 0 || !L || !B || !b.layers_dev || !c->overlap) return prepare_online(c, a, mode, L, B, n, out_dev, Pa);
+    if (n <= 0 || !L || !B || !b.dev || !c->overlap) return prepare_online(c, a, mode, L, B, n, out_dev, Pa);
     // the whole batch first, so that an error names the caller's layer index
     if (mode != CT_MODE_SPDZ2K && mode != CT_MODE_COMPACT) return fail(c, CT_EINVAL, "unknown mode");
     ct_status v = validate(c, a.max_layers, L, B, n,
@@ -1351,9 +1342,9 @@ ct_status ct_plan_create(ct_ctx *c, ct_mode mode, const ct_layer_desc *L, const 
     hipStream_t st = nullptr, side = nullptr;
     if (c->rns.scratch) pl->lane.rns = pl->side.rns = &pl->rns;
     hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
-    if (e == hipSuccess) e = lane_init(pl->lane, st, std::max(n, 1));
+    if (e == hipSuccess) e = lane_init(pl->lane, st, std::max(n, 1), c->np);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
-    if (e == hipSuccess) e = lane_init(pl->side, side, std::max(n, 1));
+    if (e == hipSuccess) e = lane_init(pl->side, side, std::max(n, 1), c->np);
     else pl->side.stream = side;
     if (e == hipSuccess) e = hipEventCreateWithFlags(&pl->fork, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&pl->join, hipEventDisableTiming);

@@ -33,17 +33,19 @@ struct RnsMemory {
 struct Lane {
     hipStream_t stream = nullptr;
     int max_layers = 0, max_probs = 0, max_jobs = 0;
+    // One block on the device and one pinned.  They begin with the tables of the call at hand (lane_place): layer
+    // records, product problems and packing jobs, then those of the other paths, at the same offsets in both, so that
+    // one copy uploads them all.  Behind the room for max_layers layers: check accumulators, results, counters.
+    uint8_t *dev = nullptr, *host = nullptr;
     LayerDev *layers_dev = nullptr, *layers_host = nullptr;
-    GemmProb *gemm_dev = nullptr, *gemm_host = nullptr;
-    PackJob *pack_dev = nullptr, *pack_host = nullptr;
+    GemmProb *gemm_dev = nullptr, *gemm_host = nullptr;           // max_probs
+    PackJob *pack_dev = nullptr, *pack_host = nullptr;            // max_jobs
     SkinnyProb *skinny_dev = nullptr, *skinny_host = nullptr;
-    // residue products: memory of the lane's context or plan (null: every product by digits; set before lane_init),
-    // and the lane's tables, one block on the device (rns_tables) and one pinned
-    RnsMemory *rns = nullptr;
-    uint8_t *rns_tables = nullptr, *rns_staging = nullptr;
     RnsJob *rns_jobs_dev = nullptr, *rns_jobs_host = nullptr;     // max_jobs
-    RnsOpen *rns_open_dev = nullptr, *rns_open_host = nullptr;    // max_layers
+    RnsOpen *rns_open_dev = nullptr, *rns_open_host = nullptr;
     RnsProb *rns_probs_dev = nullptr, *rns_probs_host = nullptr;  // max_probs
+    // residue products: memory of the lane's context or plan (null: every product by digits; set before lane_init)
+    RnsMemory *rns = nullptr;
     u128 *acc_dev = nullptr;
     ct_check_result *res_dev = nullptr, *res_host = nullptr;
     uint32_t *sync_dev = nullptr;      // counters of the persistent launch (64 bytes)
@@ -55,9 +57,9 @@ struct Lane {
     bool timed = false;                // per-launch event timing (the context's own lane only)
 };
 
-// Allocates the lane's tables for up to max_layers layers (the stream is the
-// caller's).  On failure the lane is left for lane_free.
-hipError_t lane_init(Lane &ln, hipStream_t stream, int max_layers);
+// Allocates the lane's tables for up to max_layers layers of np parties (the
+// stream is the caller's).  On failure the lane is left for lane_free.
+hipError_t lane_init(Lane &ln, hipStream_t stream, int max_layers, int np);
 void lane_free(Lane &ln);
 
 }  // namespace ct

@@ -287,9 +287,9 @@ ct_status ct_server_create(ct_ctx *ctx, const ct_server_params *p, ct_server **o
     s->slots.resize(p->slots);
     for (Slot &sl : s->slots) {
         hipError_t e = hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking);
-        if (e == hipSuccess) e = lane_init(sl.deal, sl.stream, p->max_batch);
-        if (e == hipSuccess) e = lane_init(sl.online, sl.stream, p->max_batch);
-        if (e == hipSuccess) e = lane_init(sl.check, sl.stream, p->max_batch);
+        if (e == hipSuccess) e = lane_init(sl.deal, sl.stream, p->max_batch, ctx->np);
+        if (e == hipSuccess) e = lane_init(sl.online, sl.stream, p->max_batch, ctx->np);
+        if (e == hipSuccess) e = lane_init(sl.check, sl.stream, p->max_batch, ctx->np);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.done, hipEventDisableTiming);
         if (e != hipSuccess) {
             free_slots(s);
