@@ -530,15 +530,74 @@ int fit_wshape(int M, int N) {
     return WS_64x64;
 }
 
+// K slices per tile by default: enough tiles for two rounds over the compute
+// units, equal-length tiles across problems; at least 8 slices per tile (split
+// partials cost atomics), at most MAX_STEPS_PER_SPLIT (exactness of the int32
+// diagonals).
+int64_t default_target(int64_t total_steps, int num_cus) {
+    return std::min<int64_t>(std::max<int64_t>((total_steps + 2LL * num_cus - 1) / (2LL * num_cus), 8), MAX_STEPS_PER_SPLIT);
+}
+
+// Length of a launch in K slices of a wavefront: workgroups of wg x wg outputs
+// and target slices, divided over `share` wavefronts, on num_cus compute units
+// that take one each at a time.  A workgroup's start and end take as long as
+// about 4 slices, the atomic additions of split products about 16 more (16 a
+// lane, or 4 when the wavefronts share a tile), their launch for the constant
+// terms about 3.
+int64_t gemm_length(const std::vector<GemmProb> &probs, int num_cus, int wg, int64_t target, int share) {
+    int64_t longest = 1, sum = 0;
+    bool split = false;
+    for (const auto &p : probs) {
+        const int64_t n = (int64_t)((p.K + 31) / 32) * (p.Lp2 ? 2 : 1), splits = (n + target - 1) / target;
+        const int64_t len = ((n + splits - 1) / splits + share - 1) / share + 4 + (splits > 1 ? 16 / share : 0);
+        longest = std::max(longest, len);
+        sum += len * splits * ((p.M + wg - 1) / wg) * ((p.N + wg - 1) / wg);
+        split |= splits > 1;
+    }
+    return longest * ((sum + longest * num_cus - 1) / (longest * num_cus)) + (split ? 3 : 0);
+}
+
+// Whether the wavefronts of a workgroup share the K slices of one output tile
+// (WS_K4), and into how many slices per workgroup K is then split: for launches
+// of fewer than two 64 x 64 tiles per compute unit whose configuration is left
+// to the library, if it is the shorter way by gemm_length.  Larger launches
+// keep every compute unit busy without, and read half as many fragments.
+// Measured with the launch for constant terms, us before and after:
+// 64 x 128 x 32 27.6 and 15.7, 256 x 256 x 256 39.8 and 26.0, 96 x 1024 x 1024
+// 93.7 and 57.7, 130 x 4608 x 300 131.7 and 109.9; the other way round for
+// 512 x 64 x 512 (24.7 and 32.5), which the rule leaves as it was.
+int64_t k4_target(const std::vector<GemmProb> &probs, int num_cus, const GemmTuning &tu) {
+    if (tu.tile != CT_TILE_AUTO || tu.split_target != 0) return 0;
+    int64_t tiles = 0, steps = 0, most = 0;
+    for (const auto &p : probs) {
+        const int64_t t = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64), n = (int64_t)((p.K + 31) / 32) * (p.Lp2 ? 2 : 1);
+        tiles += t;
+        steps += t * n;
+        most = std::max(most, n);
+    }
+    if (tiles >= 2LL * num_cus) return 0;
+    int64_t best = gemm_length(probs, num_cus, 64, default_target(steps, num_cus), 1), choice = 0;
+    for (int64_t t = 32; ; t += t / 8) {  // 8 slices a wavefront and more
+        const int64_t target = std::min<int64_t>(t, MAX_STEPS_PER_SPLIT), len = gemm_length(probs, num_cus, 32, target, 4);
+        if (len < best) {
+            best = len;
+            choice = target;
+        }
+        if (target >= most || target == MAX_STEPS_PER_SPLIT) return choice;
+    }
+}
+
+// staged: the products run as a launch of their own (not in the persistent one).
 int plan_gemms(std::vector<GemmProb> &probs, int num_cus, const GemmTuning &tu, int *total_tiles, bool *any_accum,
-               int eb) {
-    const int mt = gemm_mt(probs, num_cus, tu, eb);
+               int eb, bool staged) {
+    const int64_t k4 = staged ? k4_target(probs, num_cus, tu) : 0;
+    const int mt = k4 ? 1 : gemm_mt(probs, num_cus, tu, eb);
     int64_t total_steps = 0;
     for (auto &p : probs) {
         p.mt = mt;
-        p.wshape = tu.tile == CT_TILE_REGS_FIT ? fit_wshape(p.M, p.N) : WS_64x64;
-        const int wgm = p.wshape == WS_32x128 ? 32 : p.wshape == WS_128x32 ? 128 : 64 * mt;
-        const int wgn = p.wshape == WS_32x128 ? 128 : p.wshape == WS_128x32 ? 32 : 64;
+        p.wshape = k4 ? WS_K4 : tu.tile == CT_TILE_REGS_FIT ? fit_wshape(p.M, p.N) : WS_64x64;
+        const int wgm = p.wshape == WS_32x128 || k4 ? 32 : p.wshape == WS_128x32 ? 128 : 64 * mt;
+        const int wgn = p.wshape == WS_32x128 ? 128 : p.wshape == WS_128x32 || k4 ? 32 : 64;
         p.tiles_m = (p.M + wgm - 1) / wgm;
         p.tiles_n = (p.N + wgn - 1) / wgn;
         p.kt = (p.K + 31) / 32;
@@ -546,13 +605,8 @@ int plan_gemms(std::vector<GemmProb> &probs, int num_cus, const GemmTuning &tu, 
         p.group_m = std::max(1, std::min(tu.group_m, p.tiles_m));
         total_steps += (int64_t)p.tiles_m * p.tiles_n * p.nsteps;
     }
-    // K slices per tile: by default enough tiles for two rounds over the
-    // compute units, equal-length tiles across problems; at least 8 slices
-    // per tile (split partials cost atomics), at most MAX_STEPS_PER_SPLIT
-    // (exactness of the int32 diagonals).
-    int64_t target = tu.split_target > 0 ? tu.split_target : (total_steps + 2LL * num_cus - 1) / (2LL * num_cus);
-    if (target < 8) target = 8;
-    if (target > MAX_STEPS_PER_SPLIT) target = MAX_STEPS_PER_SPLIT;
+    int64_t target = k4 ? k4 : default_target(total_steps, num_cus);
+    if (tu.split_target > 0) target = std::min<int64_t>(std::max<int64_t>(tu.split_target, 8), MAX_STEPS_PER_SPLIT);
     int tile = 0;
     *any_accum = false;
     for (size_t i = 0; i < probs.size();) {
@@ -582,7 +636,8 @@ int plan_gemms(std::vector<GemmProb> &probs, int num_cus, const GemmTuning &tu, 
 ct_status run_gemms(ct_ctx *c, Lane &ln, int nprobs, int total_tiles, const GemmTuning &tu, hipStream_t st) {
     if (nprobs > 0)
         LAUNCH(c, ln, ST_RING_GEMM, launch_gemm(c->eb, ln.gemm_dev, nprobs, total_tiles, tu.xcd_remap,
-                                                ln.gemm_host[0].mt, gemm_kernel(tu), st));
+                                                ln.gemm_host[0].mt,
+                                                ln.gemm_host[0].wshape == WS_K4 ? GEMM_K4 : gemm_kernel(tu), st));
     return CT_OK;
 }
 
@@ -799,7 +854,7 @@ ct_status ct::run_deal(ct_ctx *c, Lane &ln, const ct_layer_desc *L, const ct_lay
     int total_tiles = 0;
     bool any_accum = false;
     const GemmTuning tu = c->fallback;
-    const int nm = plan_gemms(probs, c->num_cus, tu, &total_tiles, &any_accum, c->eb);
+    const int nm = plan_gemms(probs, c->num_cus, tu, &total_tiles, &any_accum, c->eb, true);
     std::copy(probs.begin(), probs.end(), ln.gemm_host);
     if ((s = upload(c, ln, n, nm, njobs, nskinny)) != CT_OK) return s;
     const Sizes sz = max_sizes(L, n);
@@ -916,7 +971,7 @@ ct_status prepare_online_np(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_de
     P.njobs = njobs;
     P.pack_tiles = plan_jobs(ln.pack_host, njobs);
     P.tu = tuning_for(c, shape_class(mode, L, n));
-    P.nm = plan_gemms(probs, c->num_cus, P.tu, &P.total_tiles, &P.any_accum, c->eb);
+    P.nm = plan_gemms(probs, c->num_cus, P.tu, &P.total_tiles, &P.any_accum, c->eb, c->launch_mode == CT_LAUNCH_STAGED);
     std::copy(probs.begin(), probs.end(), ln.gemm_host);
     if (!rns.empty())
         rns_plan(rns, ln.rns->scratch, ln.rns->bytes, ln.rns_jobs_host, ln.rns_probs_host, ln.rns_open_host, P.rns);
@@ -1082,7 +1137,7 @@ ct_status prepare_online(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_desc 
     for (int l = 0; l < n; l++) P.any_open_u |= ln.layers_host[l].fo == FO_NONE;
     P.pack_tiles = plan_jobs(ln.pack_host, njobs);
     P.tu = tuning_for(c, shape_class(mode, L, n));
-    P.nm = plan_gemms(probs, c->num_cus, P.tu, &P.total_tiles, &P.any_accum, c->eb);
+    P.nm = plan_gemms(probs, c->num_cus, P.tu, &P.total_tiles, &P.any_accum, c->eb, c->launch_mode == CT_LAUNCH_STAGED);
     std::copy(probs.begin(), probs.end(), ln.gemm_host);
     if (!rns.empty())
         rns_plan(rns, ln.rns->scratch, ln.rns->bytes, ln.rns_jobs_host, ln.rns_probs_host, ln.rns_open_host, P.rns);

@@ -692,12 +692,69 @@ __device__ __forceinline__ void rs_slice(v4i (&ca)[MT][Tile<R>::NB], v4i (&cb)[T
     }
 }
 
-template <class R, int MT>
-__device__ __forceinline__ void gemm_tile_rs(const GemmProb &P, int tm, int tn, int split) {
+// Epilogue of a WS_K4 workgroup: the four wavefronts' sums of the 32 x 32
+// outputs from row r0 and column c0 on, added through LDS (the accumulator
+// layout is store_tile_out's).
+template <class R>
+__device__ __forceinline__ void gemm_add_quarters(const GemmProb &P, const v16i (&acc)[Tile<R>::NB], int r0, int c0,
+                                                  R (*part)[16][64]) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // wavefront w finishes registers 4 w .. 4 w + 3 (rows 8 w + 4 (lane / 32) + 0 .. 3)
+    R v[16];
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        v[r] = Ring<R>::zero();
+        combine<0>(acc, r, v[r]);
+    }
+    // slot (w - w') mod 4 - 1 of wavefront w' holds wavefront w's part
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        const int owner = r >> 2, slot = (wave - owner) & 3;
+        if (slot) part[slot - 1][r][lane] = v[r];
+    }
+    __syncthreads();
+    R sum[4], base[4];
+    int64_t idx[4];
+    bool ok[4];
+    const int row0 = r0 + 8 * wave + 4 * (lane >> 5), col = c0 + (lane & 31);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        ok[i] = row0 + i < P.M && col < P.N;
+        idx[i] = (int64_t)(row0 + i) * P.N + col;
+        sum[i] = wave == 0 ? v[i] : wave == 1 ? v[4 + i] : wave == 2 ? v[8 + i] : v[12 + i];
+#pragma unroll
+        for (int q = 0; q < 3; q++) sum[i] = add(sum[i], part[q][4 * wave + i][lane]);
+    }
+    R *out = reinterpret_cast<R *>(P.out);
+    if (P.accumulate) {
+        R *cell[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) cell[i] = out + idx[i];
+        atomic_add128_n<4>(cell, sum, ok);
+        return;
+    }
+    const R *bp = reinterpret_cast<const R *>(P.base);
+#pragma unroll
+    for (int i = 0; i < 4; i++) base[i] = bp && ok[i] ? ld_nt(bp, idx[i]) : Ring<R>::zero();
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+        if (ok[i]) st_nt(out, idx[i], add(sum[i], base[i]));
+}
+
+// The products of an output tile of workgroup tile (tm, tn).  K4 (WS_K4): the
+// four wavefronts take a quarter of the tile's K slices each on the same 32 x 32
+// outputs and add their sums through `part` (gemm_add_quarters).
+template <class R, int MT, bool K4 = false>
+__device__ __forceinline__ void gemm_tile_rs(const GemmProb &P, int tm, int tn, int split, R (*part)[16][64] = nullptr) {
     constexpr int NB = Tile<R>::NB, OPB = Tile<R>::OPB;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int s_begin = split * P.steps_per_split;
-    const int s_end = min(s_begin + P.steps_per_split, P.nsteps);
+    int s_begin = split * P.steps_per_split;
+    int s_end = min(s_begin + P.steps_per_split, P.nsteps);
+    if constexpr (K4) {
+        const int per = (s_end - s_begin + 3) / 4, w = __builtin_amdgcn_readfirstlane(wave);
+        s_begin = min(s_begin + w * per, s_end);
+        s_end = min(s_begin + per, s_end);
+    }
     const int mtiles = (P.M + 63) / 64;  // row tiles of the packed left operand
 
     // The wavefront's place in the workgroup tile (WaveShape; MT stacked
@@ -705,7 +762,10 @@ __device__ __forceinline__ void gemm_tile_rs(const GemmProb &P, int tm, int tn, 
     // wavefront whose outputs all lie past M or N has nothing to store and
     // leaves (this kernel has no barriers).
     int r0, c0;
-    if (MT == 1 && P.wshape == WS_32x128) {
+    if constexpr (K4) {
+        r0 = tm * 32;
+        c0 = tn * 32;
+    } else if (MT == 1 && P.wshape == WS_32x128) {
         r0 = tm * 32;
         c0 = tn * 128 + 32 * wave;
     } else if (MT == 1 && P.wshape == WS_128x32) {
@@ -774,7 +834,8 @@ __device__ __forceinline__ void gemm_tile_rs(const GemmProb &P, int tm, int tn, 
     }
     if (nsl > 0 && (nsl & 1))
         rs_slice<R, MT, D>(fa[0], fb[0], fa[1], fb[1], t0, b0t, t0, b0t, a_off, b_off, acc);
-    store_tile_out<R, MT>(P, acc, r0, c0, 0, 0, lane);
+    if constexpr (K4) gemm_add_quarters<R>(P, acc[0], r0, c0, part);
+    else store_tile_out<R, MT>(P, acc, r0, c0, 0, 0, lane);
 }
 
 // One workgroup per output tile (grid = total_tiles): a loop over tiles
@@ -790,6 +851,24 @@ __global__ __launch_bounds__(256, 1) void k_ring_gemm_rs(const GemmProb *__restr
     const TileRef tr = decode_tile(probs, nprobs, t);
     const GemmProb P = probs[tr.prob];
     gemm_tile_rs<R, MT>(P, tr.tm, tr.tn, tr.split);
+}
+
+// The products of a launch with few output tiles (WS_K4): a workgroup takes
+// one 32 x 32 output tile, its four wavefronts a quarter of the K slices each,
+// and the partial sums are added through LDS.  Such a launch is bound by the
+// chain of a wavefront's slices (about 2 us each) with most compute units
+// idle; splitting K over workgroups instead costs an atomic addition per
+// output and split and a launch for the constant terms.
+template <class R>
+__global__ __launch_bounds__(256, 1) void k_ring_gemm_k4(const GemmProb *__restrict__ probs, int nprobs,
+                                                         int total_tiles, int xcd_remap) {
+    __shared__ R part[3][16][64];
+    const int b = blockIdx.x;
+    if (b >= total_tiles) return;
+    const int t = xcd_remap ? xcd_tile(b, total_tiles, xcd_remap) : b;
+    const TileRef tr = decode_tile(probs, nprobs, t);
+    const GemmProb P = probs[tr.prob];
+    gemm_tile_rs<R, 1, true>(P, tr.tm, tr.tn, tr.split, part);
 }
 
 // ---------------------------------------------------------------- persistent launch
@@ -905,6 +984,10 @@ hipError_t launch_online_persist(int eb, const PersistArgs &a, int wgs, hipStrea
 hipError_t launch_gemm(int eb, const GemmProb *probs_dev, int nprobs, int total_tiles, int xcd_remap, int mt,
                        int kernel, hipStream_t st) {
     if (nprobs <= 0 || total_tiles <= 0) return hipSuccess;
+    if (kernel == GEMM_K4) {
+        LAUNCH_RING(eb, k_ring_gemm_k4, dim3(total_tiles), dim3(256), st, probs_dev, nprobs, total_tiles, xcd_remap);
+        return hipGetLastError();
+    }
     if (kernel == GEMM_REGS) {
         if (eb == 8 && mt == 2)
             hipLaunchKernelGGL((k_ring_gemm_rs<r64, 2>), dim3(total_tiles), dim3(256), 0, st, probs_dev, nprobs,

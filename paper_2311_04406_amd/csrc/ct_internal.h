@@ -328,12 +328,13 @@ struct GemmProb {
 // 32 x 32 output tile each: 2 x 2 (64 x 64 outputs), 1 x 4 (32 x 128) or
 // 4 x 1 (128 x 32).  The wavefronts load their fragments independently, so
 // any arrangement reads the same packed operand tiles; the narrow ones pad a
-// product's M (or N) to 32 instead of 64.
-enum WaveShape : int { WS_64x64 = 0, WS_32x128 = 1, WS_128x32 = 2 };
+// product's M (or N) to 32 instead of 64.  WS_K4: all four on one tile, a
+// quarter of the K slices each (k_ring_gemm_k4, every problem of a launch or none).
+enum WaveShape : int { WS_64x64 = 0, WS_32x128 = 1, WS_128x32 = 2, WS_K4 = 3 };
 
 // Product kernels: operand tiles staged through LDS, or fragments streamed
 // from global memory into registers.
-enum GemmKernel : int { GEMM_LDS = 0, GEMM_REGS = 1 };
+enum GemmKernel : int { GEMM_LDS = 0, GEMM_REGS = 1, GEMM_K4 = 2 };
 
 // Launch configuration of the matrix-core products (chosen by ct_autotune).
 struct GemmTuning {

@@ -57,7 +57,7 @@ struct RnsShape {
 // Which of the layers of a call (those with N > SKINNY_MAX_N) take the residue
 // path.  Each path brings launches of its own, tens of microseconds on a small
 // call, so a few layers on the slower side follow the others (up to 100 us of
-// digit products), and a call that would gain less than 10 us, or less than
+// digit products), and a call that would gain less than 18 us, or less than
 // 80 us and keep both paths for it, stays with digits.
 inline std::vector<char> rns_choose(const std::vector<RnsShape> &s, int64_t cap) {
     std::vector<char> take(s.size(), 0);
@@ -81,7 +81,7 @@ inline std::vector<char> rns_choose(const std::vector<RnsShape> &s, int64_t cap)
         gain -= rest_loss;
         others = false;
     }
-    if (gain < (others ? 80 : 10)) take.assign(s.size(), 0);
+    if (gain < (others ? 80 : 18)) take.assign(s.size(), 0);
     return take;
 }
 
