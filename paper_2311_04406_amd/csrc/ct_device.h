@@ -41,24 +41,41 @@ __device__ __forceinline__ u128 mul64(u128 a, uint64_t b) {
 __device__ __forceinline__ u128 mad64(u128 acc, u128 a, uint64_t b) { return add(acc, mul64(a, b)); }
 __device__ __forceinline__ u128 mad(u128 acc, u128 a, u128 b) { return add(acc, mul(a, b)); }
 
+// Every element access is to global memory, which the compiler cannot tell of
+// pointers read from the layer records: without the address space it emits flat
+// instructions, which may complete out of order with LDS accesses, so that each
+// use waits for all of a wavefront's loads (never use these on LDS).
+#define CT_GLOBAL __attribute__((address_space(1)))
+typedef unsigned long long ct_u64x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t ct_u32x4 __attribute__((ext_vector_type(4)));
+template <class T, class U>
+__device__ __forceinline__ const CT_GLOBAL T *global_ptr(const U *p) {
+    return (const CT_GLOBAL T *)reinterpret_cast<const T *>(p);
+}
+template <class T, class U>
+__device__ __forceinline__ CT_GLOBAL T *global_ptr(U *p) {
+    return (CT_GLOBAL T *)reinterpret_cast<T *>(p);
+}
+
 __device__ __forceinline__ u128 ld(const u128 *p, int64_t i) {
-    const ulonglong2 v = reinterpret_cast<const ulonglong2 *>(p)[i];
+    const ct_u64x2 v = global_ptr<ct_u64x2>(p)[i];
     return u128{v.x, v.y};
 }
 // A load of streamed data that is not read again soon (non-temporal hint:
 // it does not displace reused lines from the caches).
 __device__ __forceinline__ u128 ld_nt(const u128 *p, int64_t i) {
-    const uint64_t *q = reinterpret_cast<const uint64_t *>(p) + 2 * i;
-    return u128{__builtin_nontemporal_load(q), __builtin_nontemporal_load(q + 1)};
+    const ct_u64x2 v = __builtin_nontemporal_load(global_ptr<ct_u64x2>(p) + i);
+    return u128{v.x, v.y};
 }
-__device__ __forceinline__ void st(u128 *p, int64_t i, u128 v) {
-    reinterpret_cast<ulonglong2 *>(p)[i] = make_ulonglong2(v.lo, v.hi);
-}
+__device__ __forceinline__ void st(u128 *p, int64_t i, u128 v) { global_ptr<ct_u64x2>(p)[i] = ct_u64x2{v.lo, v.hi}; }
 // A store of streamed output that is not read again soon (non-temporal hint);
 // one 16-byte store.
-typedef unsigned long long ct_u64x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void st_nt(u128 *p, int64_t i, u128 v) {
-    __builtin_nontemporal_store(ct_u64x2{v.lo, v.hi}, reinterpret_cast<ct_u64x2 *>(p) + i);
+    __builtin_nontemporal_store(ct_u64x2{v.lo, v.hi}, global_ptr<ct_u64x2>(p) + i);
+}
+// An atomic addition of two's complement 64-bit words in global memory.
+__device__ __forceinline__ unsigned long long atomic_add64(unsigned long long *p, unsigned long long v) {
+    return __hip_atomic_fetch_add(global_ptr<unsigned long long>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Exact accumulation of many values into four 64-bit cells with atomics
@@ -70,7 +87,7 @@ __device__ __forceinline__ void atomic_add_limbs(unsigned long long *cell, u128 
     const unsigned long long l[4] = {v.lo & 0xffffffffull, v.lo >> 32, v.hi & 0xffffffffull, v.hi >> 32};
 #pragma unroll
     for (int j = 0; j < 4; j++)
-        if (l[j]) atomicAdd(cell + j, l[j]);
+        if (l[j]) atomic_add64(cell + j, l[j]);
 }
 __device__ __forceinline__ void from_limbs(const unsigned long long *cell, u128 &v) {
     const unsigned long long l0 = cell[0], l1 = cell[1], l2 = cell[2], l3 = cell[3];
@@ -84,10 +101,10 @@ __device__ __forceinline__ void from_limbs(const unsigned long long *cell, u128 
 // exactly once, so the result is the mod-2^128 sum whatever the order.
 __device__ __forceinline__ void atomic_add128(u128 *p, u128 v) {
     unsigned long long *q = reinterpret_cast<unsigned long long *>(p);
-    const unsigned long long old = atomicAdd(q, (unsigned long long)v.lo);
+    const unsigned long long old = atomic_add64(q, v.lo);
     const unsigned long long carry = (old + v.lo < old) ? 1ull : 0ull;
     const unsigned long long hi = v.hi + carry;
-    if (hi) atomicAdd(q + 1, hi);
+    if (hi) atomic_add64(q + 1, hi);
 }
 
 // Orders a wavefront's LDS writes before its later LDS reads by other lanes
@@ -108,13 +125,13 @@ __device__ __forceinline__ void atomic_add128_n(u128 *const (&p)[NV], const u128
 #pragma unroll
     for (int i = 0; i < NV; i++) {
         old[i] = 0;
-        if (ok[i]) old[i] = atomicAdd(reinterpret_cast<unsigned long long *>(p[i]), (unsigned long long)v[i].lo);
+        if (ok[i]) old[i] = atomic_add64(reinterpret_cast<unsigned long long *>(p[i]), v[i].lo);
     }
     __asm__ volatile("" ::: "memory");
 #pragma unroll
     for (int i = 0; i < NV; i++) {
         const unsigned long long hi = v[i].hi + (old[i] + v[i].lo < old[i] ? 1ull : 0ull);
-        if (ok[i] && hi) atomicAdd(reinterpret_cast<unsigned long long *>(p[i]) + 1, hi);
+        if (ok[i] && hi) atomic_add64(reinterpret_cast<unsigned long long *>(p[i]) + 1, hi);
     }
 }
 
@@ -173,24 +190,24 @@ __device__ __forceinline__ r64 mul(r64 a, r64 b) { return r64{a.v * b.v}; }
 __device__ __forceinline__ r64 mul64(r64 a, uint64_t b) { return r64{a.v * b}; }
 __device__ __forceinline__ r64 mad64(r64 acc, r64 a, uint64_t b) { return r64{acc.v + a.v * b}; }
 __device__ __forceinline__ r64 mad(r64 acc, r64 a, r64 b) { return r64{acc.v + a.v * b.v}; }
-__device__ __forceinline__ r64 ld(const r64 *p, int64_t i) { return p[i]; }
-__device__ __forceinline__ r64 ld_nt(const r64 *p, int64_t i) { return r64{__builtin_nontemporal_load(&p[i].v)}; }
-__device__ __forceinline__ void st(r64 *p, int64_t i, r64 v) { p[i] = v; }
-__device__ __forceinline__ void st_nt(r64 *p, int64_t i, r64 v) { __builtin_nontemporal_store(v.v, &p[i].v); }
+__device__ __forceinline__ r64 ld(const r64 *p, int64_t i) { return r64{global_ptr<uint64_t>(p)[i]}; }
+__device__ __forceinline__ r64 ld_nt(const r64 *p, int64_t i) { return r64{__builtin_nontemporal_load(global_ptr<uint64_t>(p) + i)}; }
+__device__ __forceinline__ void st(r64 *p, int64_t i, r64 v) { global_ptr<uint64_t>(p)[i] = v.v; }
+__device__ __forceinline__ void st_nt(r64 *p, int64_t i, r64 v) { __builtin_nontemporal_store((uint64_t)v.v, global_ptr<uint64_t>(p) + i); }
 __device__ __forceinline__ void atomic_add_limbs(unsigned long long *cell, r64 v) {
     const unsigned long long l0 = v.v & 0xffffffffull, l1 = v.v >> 32;
-    if (l0) atomicAdd(cell, l0);
-    if (l1) atomicAdd(cell + 1, l1);
+    if (l0) atomic_add64(cell, l0);
+    if (l1) atomic_add64(cell + 1, l1);
 }
 __device__ __forceinline__ void from_limbs(const unsigned long long *cell, r64 &v) { v = r64{cell[0] + (cell[1] << 32)}; }
 __device__ __forceinline__ void atomic_add128(r64 *p, r64 v) {
-    atomicAdd(reinterpret_cast<unsigned long long *>(p), (unsigned long long)v.v);
+    atomic_add64(reinterpret_cast<unsigned long long *>(p), v.v);
 }
 template <int NV>
 __device__ __forceinline__ void atomic_add128_n(r64 *const (&p)[NV], const r64 (&v)[NV], const bool (&ok)[NV]) {
 #pragma unroll
     for (int i = 0; i < NV; i++)
-        if (ok[i]) atomicAdd(reinterpret_cast<unsigned long long *>(p[i]), (unsigned long long)v[i].v);
+        if (ok[i]) atomic_add64(reinterpret_cast<unsigned long long *>(p[i]), v[i].v);
 }
 __device__ __forceinline__ r64 shfl_xor128(r64 v, int m) { return r64{__shfl_xor(v.v, m, 64)}; }
 __device__ __forceinline__ r64 wave_sum(r64 v) {

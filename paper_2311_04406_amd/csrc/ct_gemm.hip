@@ -182,10 +182,10 @@ __device__ __forceinline__ void pack_body(const PackJob *__restrict__ jobs, int 
         }
         write_planes<NW>(tile, plane_off(j, kk), w);
         __syncthreads();
-        uint4 *dst = reinterpret_cast<uint4 *>(reinterpret_cast<R *>(J.dst) + ((int64_t)tm * J.kt + ks) * TILE_ELEMS);
+        CT_GLOBAL ct_u32x4 *dst = global_ptr<ct_u32x4>(reinterpret_cast<R *>(J.dst) + ((int64_t)tm * J.kt + ks) * TILE_ELEMS);
 #pragma unroll
         for (int i = 0; i < OPBYTES / 16 / 256; i++)
-            dst[i * 256 + tid] = reinterpret_cast<const uint4 *>(tile)[i * 256 + tid];
+            dst[i * 256 + tid] = reinterpret_cast<const ct_u32x4 *>(tile)[i * 256 + tid];
         __syncthreads();
     }
 }
@@ -212,18 +212,58 @@ hipError_t launch_pack(int eb, const PackJob *jobs_dev, int njobs, int total_til
 // k_open_u and of k_pack's right-operand jobs, without reading [B]_p and U a
 // second time.  One workgroup per 64 (n) x 32 (k) tile, laid out as k_pack
 // lays out a right operand's tile: lane j takes column n = 64 tn + j,
-// wavefront w the 8 rows k = 32 ks + 8 w + i; the rows' compressions are
-// summed over the wavefront and added atomically, once per row and tile.
+// wavefront w the 8 rows k = 32 ks + 8 w + i.  The rows' compressions are
+// summed over the wavefront all together (halving the rows a lane carries at
+// each exchange: 10 exchanges for the 8 rows, not 48) and added atomically,
+// once per row and tile, by one lane per row.
 template <class R>
 __device__ __forceinline__ void store_tile(uint8_t *tile, int off, const uint32_t (&w)[8][Tile<R>::NW], u128 *dst) {
     constexpr int OPB = Tile<R>::OPB;
     write_planes<Tile<R>::NW>(tile, off, w);
     __syncthreads();
-    uint4 *d = reinterpret_cast<uint4 *>(dst);
+    CT_GLOBAL ct_u32x4 *d = global_ptr<ct_u32x4>(dst);
 #pragma unroll
-    for (int i = 0; i < OPB / 16 / 256; i++) d[i * 256 + threadIdx.x] = reinterpret_cast<const uint4 *>(tile)[i * 256 + threadIdx.x];
+    for (int i = 0; i < OPB / 16 / 256; i++) d[i * 256 + threadIdx.x] = reinterpret_cast<const ct_u32x4 *>(tile)[i * 256 + threadIdx.x];
     __syncthreads();
 }
+
+// Three sums over the wavefront for each of 8 rows, row by row: of the rows
+// i and i + 2^j that meet at level j, lanes with bit (32 >> j) set go on with
+// the second and the others with the first.  After row 7 and finish() lane l
+// holds the totals of row (l >> 5 & 1) + 2 (l >> 4 & 1) + 4 (l >> 3 & 1).
+template <class R>
+struct RowSums {
+    R part[3][3];  // a pending value per level (three of each)
+    R sum[3];
+    __device__ __forceinline__ static R meet(R first, R second, int bit) {
+        const bool up = threadIdx.x & bit;
+        return add(up ? second : first, shfl_xor128(up ? first : second, bit));
+    }
+    __device__ __forceinline__ void row(int i, const R (&v)[3]) {  // i: a constant after unrolling
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            R x = v[q];
+            if (i & 1) {
+                x = meet(part[0][q], x, 32);
+                if (i & 2) {
+                    x = meet(part[1][q], x, 16);
+                    if (i & 4) sum[q] = meet(part[2][q], x, 8);
+                    else part[2][q] = x;
+                } else {
+                    part[1][q] = x;
+                }
+            } else {
+                part[0][q] = x;
+            }
+        }
+    }
+    __device__ __forceinline__ void finish() {
+#pragma unroll
+        for (int q = 0; q < 3; q++)
+#pragma unroll
+            for (int m = 4; m >= 1; m >>= 1) sum[q] = add(sum[q], shfl_xor128(sum[q], m));
+    }
+};
 
 template <class R>
 __device__ __forceinline__ void open_pack_body(const LayerDev *__restrict__ Ls, int flags, const Grid &g) {
@@ -245,44 +285,60 @@ __device__ __forceinline__ void open_pack_body(const LayerDev *__restrict__ Ls, 
     const uint64_t xn = compact && n < N ? Ring<R>::mod_s(sdraw(L.key[K_CHI], (uint64_t)n)) : 0;
     R chk[3] = {Ring<R>::zero(), Ring<R>::zero(), Ring<R>::zero()};
     uint32_t wb0[8][NW], wb1[8][NW], wu[8][NW];
+    RowSums<R> rows;
+    // the shares of a row come in while the row before is used
+    struct In {
+        R y0, y1, b0, b1, tb0, tb1, ty0, ty1;
+    };
+    auto load = [&](int i, In &v) {
+        const int64_t k = (int64_t)ks * 32 + kk + i;
+        v.y0 = v.y1 = v.b0 = v.b1 = v.tb0 = v.tb1 = v.ty0 = v.ty1 = Ring<R>::zero();
+        if (k < K && n < N) {
+            const int64_t e = k * N + n;
+            v.y0 = ld_nt(P<R>(L.Y[0]), e);
+            v.y1 = ld_nt(P<R>(L.Y[1]), e);
+            v.b0 = ld_nt(P<R>(L.B[0]), e);
+            v.b1 = ld_nt(P<R>(L.B[1]), e);
+            if (need_tb) {
+                v.tb0 = ld_nt(P<R>(L.tB[0]), e);
+                v.tb1 = ld_nt(P<R>(L.tB[1]), e);
+            }
+            if (check) {
+                v.ty0 = ld_nt(P<R>(L.tY[0]), e);
+                v.ty1 = ld_nt(P<R>(L.tY[1]), e);
+            }
+        }
+    };
+    In in[2];
+    load(0, in[0]);
 #pragma unroll
     for (int i = 0; i < 8; i++) {
         const int64_t k = (int64_t)ks * 32 + kk + i;
-        R b0 = Ring<R>::zero(), b1 = Ring<R>::zero(), u = Ring<R>::zero();
-        R tb0 = Ring<R>::zero(), tb1 = Ring<R>::zero();
+        const In &v = in[i & 1];
+        if (i + 1 < 8) load(i + 1, in[(i + 1) & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        const R b0 = v.b0, b1 = v.b1, tb0 = v.tb0, tb1 = v.tb1, u = add(sub(v.y0, v.b0), sub(v.y1, v.b1));
         if (k < K && n < N) {
             const int64_t e = k * N + n;
-            // all loads of the element before the store of U
-            const R y0 = ld_nt(P<R>(L.Y[0]), e), y1 = ld_nt(P<R>(L.Y[1]), e);
-            b0 = ld_nt(P<R>(L.B[0]), e);
-            b1 = ld_nt(P<R>(L.B[1]), e);
-            R ty0 = Ring<R>::zero(), ty1 = Ring<R>::zero();
-            if (need_tb) {
-                tb0 = ld_nt(P<R>(L.tB[0]), e);
-                tb1 = ld_nt(P<R>(L.tB[1]), e);
-            }
-            if (check) {
-                ty0 = ld_nt(P<R>(L.tY[0]), e);
-                ty1 = ld_nt(P<R>(L.tY[1]), e);
-            }
-            u = add(sub(y0, b0), sub(y1, b1));
             // U is read again only by the column tags of a layer compressed along M
             if (L.cm) st(P<R>(L.U), e, u);
             else st_nt(P<R>(L.U), e, u);
             if (check) {
                 const uint64_t x = Ring<R>::mod_s(sdraw(kcu, (uint64_t)e));
-                chk[0] = mad64(chk[0], sub(ty0, tb0), x);
-                chk[1] = mad64(chk[1], sub(ty1, tb1), x);
+                chk[0] = mad64(chk[0], sub(v.ty0, tb0), x);
+                chk[1] = mad64(chk[1], sub(v.ty1, tb1), x);
                 chk[2] = mad64(chk[2], u, x);
             }
         }
-        if (compact && k < K) {  // k is the same for the whole wavefront
-            const R v0 = wave_sum(mul64(u, xn)), v1 = wave_sum(mul64(tb0, xn)), v2 = wave_sum(mul64(tb1, xn));
-            if (lane == 0) add_cells<3>(P<R>(L.cvec), {o.Uc, o.tBc0, o.tBc1}, k, {v0, v1, v2});
-        }
+        if (compact) rows.row(i, {mul64(u, xn), mul64(tb0, xn), mul64(tb1, xn)});
         to_digits(b0, wb0[i]);
         to_digits(b1, wb1[i]);
         to_digits(u, wu[i]);
+    }
+    if (compact) {
+        rows.finish();
+        const int64_t k = (int64_t)ks * 32 + kk + ((lane >> 5 & 1) | (lane >> 4 & 1) << 1 | (lane >> 3 & 1) << 2);
+        if ((lane & 7) == 0 && k < K) add_cells<3>(P<R>(L.cvec), {o.Uc, o.tBc0, o.tBc1}, k, rows.sum);
     }
     const int64_t toff = ((int64_t)tn * kt + ks) * TILE_ELEMS;
     const int off = plane_off(lane, kk);
@@ -293,7 +349,7 @@ __device__ __forceinline__ void open_pack_body(const LayerDev *__restrict__ Ls, 
 }
 
 template <class R>
-__global__ __launch_bounds__(256) void k_open_pack(const LayerDev *__restrict__ Ls, int flags) {
+__global__ __launch_bounds__(256, 2) void k_open_pack(const LayerDev *__restrict__ Ls, int flags) {
     open_pack_body<R>(Ls, flags, hw_grid());
 }
 

@@ -152,7 +152,7 @@ __device__ __forceinline__ void convert(const u128 (&x)[16], int side, uint8_t *
         }
 #pragma unroll
         for (int r = 0; r < 4; r++)
-            *reinterpret_cast<uint4 *>(dst + (int64_t)(4 * g + r) * plane) = make_uint4(out[r][0], out[r][1], out[r][2], out[r][3]);
+            *global_ptr<ct_u32x4>(dst + (int64_t)(4 * g + r) * plane) = ct_u32x4{out[r][0], out[r][1], out[r][2], out[r][3]};
     }
 }
 
@@ -485,8 +485,8 @@ __device__ __forceinline__ void rns_tile(const RnsProb &P, int q, int tm, int tn
             for (int i = 0; i < WI; i++)
 #pragma unroll
                 for (int j = 0; j < WJ; j++) {
-                    uint4 v = make_uint4(0, 0, 0, 0);
-                    if (rm0 + i < mb && rn0 + j < nb) v = *reinterpret_cast<const uint4 *>(res + tile_off(o, i, j));
+                    ct_u32x4 v = ct_u32x4{0, 0, 0, 0};
+                    if (rm0 + i < mb && rn0 + j < nb) v = *global_ptr<ct_u32x4>(res + tile_off(o, i, j));
                     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
                     for (int r = 0; r < 16; r++) acc[o][i][j][r] = (int)(int8_t)(w[r >> 2] >> (8 * (r & 3)));
@@ -647,7 +647,7 @@ __device__ __forceinline__ void rns_tile(const RnsProb &P, int q, int tm, int tn
                     }
                     w[d] = pack4(b[0], b[1], b[2], b[3]);
                 }
-                if (rm0 + i < mb && rn0 + j < nb) *reinterpret_cast<uint4 *>(res + tile_off(o, i, j)) = make_uint4(w[0], w[1], w[2], w[3]);
+                if (rm0 + i < mb && rn0 + j < nb) *global_ptr<ct_u32x4>(res + tile_off(o, i, j)) = ct_u32x4{w[0], w[1], w[2], w[3]};
             }
 }
 
@@ -717,9 +717,9 @@ __global__ __launch_bounds__(256, 2) void k_rns_fold(const RnsProb *__restrict__
     const RnsProb &P = probs[lo];
     const int tiles = P.mb * P.nb, local = item - P.fold_begin;
     const int o = local / tiles, tile = local - o * tiles, rm = tile / P.nb, rn = tile - rm * P.nb;
-    const uint4 *src = reinterpret_cast<const uint4 *>(P.res + ((int64_t)o * tiles + tile) * 1024) + lane;
-    const int64_t step = (int64_t)P.outs * tiles * 64;  // uint4 per modulus
-    uint4 y[RNS_N];
+    const CT_GLOBAL ct_u32x4 *src = global_ptr<ct_u32x4>(P.res + ((int64_t)o * tiles + tile) * 1024) + lane;
+    const int64_t step = (int64_t)P.outs * tiles * 64;  // 16 bytes a lane, per modulus
+    ct_u32x4 y[RNS_N];
 #pragma unroll
     for (int q = 0; q < RNS_N; q++) y[q] = src[q * step];
     v4i wf[GROUPS], wq[GROUPS];
@@ -742,7 +742,7 @@ __global__ __launch_bounds__(256, 2) void k_rns_fold(const RnsProb *__restrict__
             uint32_t a[4];
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                const uint4 v = y[4 * h + j];
+                const ct_u32x4 v = y[4 * h + j];
                 a[j] = d == 0 ? v.x : d == 1 ? v.y : d == 2 ? v.z : v.w;
             }
             transpose4(a, b[h]);
