@@ -559,14 +559,14 @@ int64_t gemm_length(const std::vector<GemmProb> &probs, int num_cus, int wg, int
 
 // Whether the wavefronts of a workgroup share the K slices of one output tile
 // (WS_K4), and into how many slices per workgroup K is then split: for launches
-// of fewer than two 64 x 64 tiles per compute unit whose configuration is left
-// to the library, if it is the shorter way by gemm_length.  Larger launches
+// of fewer than two 64 x 64 tiles per compute unit (k = s = 32, with a quarter
+// of the products per fragment: half a tile) whose configuration is left to the library, if it is the shorter way by gemm_length.  Larger launches
 // keep every compute unit busy without, and read half as many fragments.
 // Measured with the launch for constant terms, us before and after:
 // 64 x 128 x 32 27.6 and 15.7, 256 x 256 x 256 39.8 and 26.0, 96 x 1024 x 1024
 // 93.7 and 57.7, 130 x 4608 x 300 131.7 and 109.9; the other way round for
 // 512 x 64 x 512 (24.7 and 32.5), which the rule leaves as it was.
-int64_t k4_target(const std::vector<GemmProb> &probs, int num_cus, const GemmTuning &tu) {
+int64_t k4_target(const std::vector<GemmProb> &probs, int num_cus, const GemmTuning &tu, int eb) {
     if (tu.tile != CT_TILE_AUTO || tu.split_target != 0) return 0;
     int64_t tiles = 0, steps = 0, most = 0;
     for (const auto &p : probs) {
@@ -575,7 +575,7 @@ int64_t k4_target(const std::vector<GemmProb> &probs, int num_cus, const GemmTun
         steps += t * n;
         most = std::max(most, n);
     }
-    if (tiles >= 2LL * num_cus) return 0;
+    if (tiles >= (eb == 8 ? num_cus / 2 : 2 * num_cus)) return 0;
     int64_t best = gemm_length(probs, num_cus, 64, default_target(steps, num_cus), 1), choice = 0;
     for (int64_t t = 32; ; t += t / 8) {  // 8 slices a wavefront and more
         const int64_t target = std::min<int64_t>(t, MAX_STEPS_PER_SPLIT), len = gemm_length(probs, num_cus, 32, target, 4);
@@ -590,7 +590,7 @@ int64_t k4_target(const std::vector<GemmProb> &probs, int num_cus, const GemmTun
 // staged: the products run as a launch of their own (not in the persistent one).
 int plan_gemms(std::vector<GemmProb> &probs, int num_cus, const GemmTuning &tu, int *total_tiles, bool *any_accum,
                int eb, bool staged) {
-    const int64_t k4 = staged ? k4_target(probs, num_cus, tu) : 0;
+    const int64_t k4 = staged ? k4_target(probs, num_cus, tu, eb) : 0;
     const int mt = k4 ? 1 : gemm_mt(probs, num_cus, tu, eb);
     int64_t total_steps = 0;
     for (auto &p : probs) {
