@@ -247,6 +247,7 @@ void fill_layer(const ct_ctx *c, u128 *acc, const ct_layer_desc &d, const ct_lay
     o.row_segs = (int32_t)((d.K + o.row_seg - 1) / o.row_seg);
     o.cm_rows = (int32_t)cm_rb(d.M, d.K, d.N);
     o.cm_items = (int32_t)cm_items(d.M, d.K, d.N);
+    o.cm_share = cm_share(d.M, d.K, d.N) ? 1 : 0;
     o.E = reinterpret_cast<u128 *>(b.E);
     o.U = reinterpret_cast<u128 *>(b.U);
     o.D = reinterpret_cast<u128 *>(b.D);
@@ -284,8 +285,8 @@ Sizes max_sizes(const ct_layer_desc *L, int n) {
         if (CT_COMPRESS_ALONG_M(d.M, d.N, d.compress)) {
             // column-strip row pass, column sweeps of the M x N pass and of the compact products
             s.cm = true;
-            s.row_items = std::max(s.row_items, cm_items(d.M, d.K, d.N));
-            s.mn_items = std::max(s.mn_items, col_sweep_items(d.M, d.N));
+            s.row_items = std::max(s.row_items, (cm_share(d.M, d.K, d.N) ? COL_WAVES : 1) * cm_items(d.M, d.K, d.N));
+            s.mn_items = std::max(s.mn_items, COL_WAVES * col_sweep_items(d.M, d.N));
             s.col_tag = std::max(s.col_tag, col_sweep_items(d.K, d.N));
         }
         if (d.N <= SKINNY_MAX_N) {
@@ -1161,7 +1162,9 @@ ct_status prepare_online(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_desc 
         const int64_t N = L[l].N;
         const int v = N > SKINNY_MAX_N ? 0 : (N <= 1 ? 1 : (N <= 2 ? 2 : (N <= 4 ? 4 : SKINNY_MAX_N)));
         if (ln.layers_host[l].fo == FO_RNS) P.variants |= 1 << VARIANT_E;
-        else P.variants |= 1 << (compact && CT_COMPRESS_ALONG_M(L[l].M, N, L[l].compress) ? VARIANT_CM + v : v);
+        else if (compact && CT_COMPRESS_ALONG_M(L[l].M, N, L[l].compress))
+            P.variants |= 1 << ((ln.layers_host[l].cm_share ? VARIANT_CM_SHARED : VARIANT_CM) + cm_index(v));
+        else P.variants |= 1 << v;
     }
     return CT_OK;
 }

@@ -94,8 +94,9 @@ struct LayerDev {
     int32_t fo;
     int32_t out_index;          // position of the layer's check record in the caller's result array
     int32_t row_seg, row_segs;  // row pass: elements of an item, items per row (row_seg below)
-    int32_t cm_rows;            // the same compressing along M: rows of an item (cm_rb below)
-    int32_t cm_items;           // and the number of items
+    int32_t cm_rows;            // the same compressing along M: rows of a wavefront (cm_rb below)
+    int32_t cm_items;           // and the number of items (of a workgroup with cm_share, else of a wavefront)
+    int32_t cm_share;
     u128 *rp[3];
 };
 
@@ -202,43 +203,57 @@ __host__ __device__ inline int row_variant(int64_t N) {
 // passes.
 __host__ __device__ inline bool np_fused_row(int64_t N) { return N > SKINNY_MAX_N || N <= 2; }
 
-// Row pass of a layer compressed along M: lanes own columns; a wavefront
-// takes a strip of cm_cw(N) * 64 columns over cm_rb(M, K, N) rows and keeps the
-// column sums chi_m E_mk, chi_m [tA]_p,mk in registers until its rows are done
+// Row pass of a layer compressed along M: lanes own columns; a wavefront takes
+// a strip of cm_cw(N) * 64 columns over up to CM_RB rows and keeps the column
+// sums chi_m E_mk, chi_m [tA]_p,mk in registers until its rows are done
 // (narrower strips for skinny layers, whose row products take registers too).
-// At most CM_RB rows, fewer while the layer has less than CM_ITEMS items: its
-// rows come one after another, a few us each, while an item's end costs three
-// atomic additions per column.  512 x 4608 x 49 took 167 us with 32 rows, 102
-// with 8 (1152 items), 110 with 4 and 137 with 2 (its 377 MB take 80);
-// 64 x 1000 x 3 took 182 us with 32 rows, about 30 with 2.
-constexpr int CM_RB = 32;
-constexpr int64_t CM_ITEMS = 1024, CM_RB_MIN = 2;
+// A layer with fewer than CM_WAVES such wavefronts (or more than CM_ADDS row
+// blocks) shares: its rows come one after another, a few us each, and the
+// atomic additions of a column follow one another, so its wavefronts take fewer
+// rows, and the four of a workgroup, on neighbouring rows, add their sums
+// before they go out.  512 x 4608 x 49 took 167 us with 32 rows a wavefront, 102
+// with 8, 90 shared (its 377 MB take 80); 1024^3 175, 79 and 48; 3000 x 64 x 2000
+// 53, 76 (with 2 rows) and 22.  Layers with enough wavefronts are slower shared:
+// 3104 us for 4096 x 25088 x 1 by wavefronts, 3180 shared.
+constexpr int CM_RB = 32, COL_WAVES = 4;
+constexpr int64_t CM_WAVES = 1024, CM_RB_MIN = 2, CM_ADDS = 256;
 __host__ __device__ constexpr int cm_cw_variant(int ns) { return ns == 0 || ns == 1 ? 4 : (ns == 2 ? 2 : 1); }
 __host__ __device__ inline int cm_cw(int64_t N) {
     return cm_cw_variant(N > 8 ? 0 : (N <= 1 ? 1 : (N <= 2 ? 2 : (N <= 4 ? 4 : 8))));
 }
-// Bit of the row-pass variant set: 1 << v for k_row_pass<v>, 1 << (VARIANT_CM + v)
-// for k_row_pass_cm<v> (v = 0, 1, 2, 4, 8).
-// Bit VARIANT_E: k_row_pass_e, the pass of FO_RNS layers, which reads the opened E.
-constexpr int VARIANT_E = 9;
-constexpr int VARIANT_CM = 16;
+// Bits of the row-pass variant set: v for k_row_pass<v>, VARIANT_E for
+// k_row_pass_e (the pass of FO_RNS layers, which reads the opened E),
+// VARIANT_CM + cm_index(v) for k_row_pass_cm<v> (v = 0, 1, 2, 4, 8), and
+// VARIANT_CM_SHARED + cm_index(v) for the same with shared items.
+constexpr int VARIANT_E = 9, VARIANT_CM = 16, VARIANT_CM_SHARED = 21;
+constexpr int cm_index(int v) { return v == 8 ? 4 : v == 4 ? 3 : v; }
 __host__ __device__ inline int64_t cm_strips(int64_t K, int cw) { return (K + 64 * cw - 1) / (64 * cw); }
+inline bool cm_share(int64_t M, int64_t K, int64_t N) {
+    const int64_t blocks = (M + CM_RB - 1) / CM_RB;
+    return cm_strips(K, cm_cw(N)) * blocks < CM_WAVES || blocks > CM_ADDS;
+}
 inline int64_t cm_rb(int64_t M, int64_t K, int64_t N) {
     const int64_t strips = cm_strips(K, cm_cw(N));
     int64_t rb = CM_RB;
-    while (rb > CM_RB_MIN && strips * ((M + rb - 1) / rb) < CM_ITEMS) rb /= 2;
+    if (cm_share(M, K, N))
+        while (rb > CM_RB_MIN && strips * ((M + rb - 1) / rb) < CM_WAVES && M <= CM_ADDS * COL_WAVES * (rb / 2)) rb /= 2;
     return rb;
 }
 inline int64_t cm_items(int64_t M, int64_t K, int64_t N) {
-    const int64_t rb = cm_rb(M, K, N);
-    return cm_strips(K, cm_cw(N)) * ((M + rb - 1) / rb);
+    const int64_t rows = (cm_share(M, K, N) ? COL_WAVES : 1) * cm_rb(M, K, N);
+    return cm_strips(K, cm_cw(N)) * ((M + rows - 1) / rows);
 }
 
-// Column sweep (sums down the columns of a rows x N matrix): wavefront items
-// of rb groups of 64 / G rows (N <= 32, G = pow2ceil(N); one atomic per column
-// per item) or of 64 columns x rb rows (one per lane).  rb = col_sweep_rb keeps
-// the atomic additions per column near 256 at most (same-address atomics
-// serialize) without starving the sweep of wavefronts.
+// Column sweep (sums down the columns of a rows x N matrix): workgroup items of
+// COL_WAVES wavefronts, each with rb groups of 64 / G rows (N <= 32,
+// G = pow2ceil(N)) or with 64 columns x rb rows (one per lane); one atomic per
+// column per item.  Additions to the same address follow one another, about
+// 0.1 us each, so rb = col_sweep_rb keeps them near COL_ADDS per column at
+// most, without starving the sweep of wavefronts.
+// One wavefront per item and 256 additions took 33 us in k_col_tag of
+// 512 x 4608 x 49 and 67 us in k_post of 1024^3; workgroup items took 33, 23,
+// 19 and 23 us (46, 45, 47 and 67) with 32, 64, 128 and 256.
+constexpr int64_t COL_ADDS = 128, COL_RB_MIN = 4;
 __host__ __device__ inline int64_t col_sweep_group(int64_t N) {
     int64_t g = 1;
     while (g < N) g <<= 1;
@@ -246,19 +261,19 @@ __host__ __device__ inline int64_t col_sweep_group(int64_t N) {
 }
 __host__ __device__ inline int64_t col_sweep_rb(int64_t rows, int64_t N) {
     if (N <= 32) {
-        const int64_t per = (64 / col_sweep_group(N)) * 256, rb = (rows + per - 1) / per;
+        const int64_t per = (64 / col_sweep_group(N)) * COL_WAVES * COL_ADDS, rb = (rows + per - 1) / per;
         return rb < 1 ? 1 : rb;
     }
-    const int64_t rb = (rows + 255) / 256;
-    return rb < 4 ? 4 : rb;
+    const int64_t rb = (rows + COL_WAVES * COL_ADDS - 1) / (COL_WAVES * COL_ADDS);
+    return rb < COL_RB_MIN ? COL_RB_MIN : rb;
 }
 __host__ __device__ inline int64_t col_sweep_items(int64_t rows, int64_t N) {
     const int64_t rb = col_sweep_rb(rows, N);
     if (N <= 32) {
-        const int64_t per = (64 / col_sweep_group(N)) * rb;
+        const int64_t per = (64 / col_sweep_group(N)) * COL_WAVES * rb;
         return (rows + per - 1) / per;
     }
-    return ((N + 63) / 64) * ((rows + rb - 1) / rb);
+    return ((N + 63) / 64) * ((rows + COL_WAVES * rb - 1) / (COL_WAVES * rb));
 }
 
 // Operands of the matrix-core products are converted once into "digit

@@ -282,10 +282,12 @@ hipError_t launch_open_u(int eb, const LayerDev *L, int n, int flags, int64_t ma
 // besides opening E, checking it and (N <= SKINNY_MAX_N) forming the output
 // products, it compresses E and [tA]_p down the columns,
 //   E^c_k = sum_m chi_m E_mk,  [tA^c]_p,k = sum_m chi_m [tA]_p,mk  (Fig. 4 along M).
-// Work items are strips of cm_cw(N) * 64 columns over cm_rb(M, K, N) rows, ordered
-// row-block-major so that concurrent wavefronts read neighbouring columns of
-// the same rows and add their column sums to different addresses.
-template <class R, int NS>
+// Work items are strips of cm_cw(N) * 64 columns over cm_rb(M, K, N) rows per
+// wavefront, ordered row-block-major so that concurrent workgroups read
+// neighbouring columns of the same rows and add their column sums to different
+// addresses.
+// SHARE: an item is a workgroup's, its wavefronts on neighbouring rows.
+template <class R, int NS, bool SHARE>
 __device__ __forceinline__ void row_pass_cm(const LayerDev &L, int flags, R (&chk)[3]) {
     const int lane = threadIdx.x & 63;
     const int64_t M = L.M, K = L.K, N = L.N;
@@ -301,11 +303,14 @@ __device__ __forceinline__ void row_pass_cm(const LayerDev &L, int flags, R (&ch
     static_assert(CM_RB <= 64, "one lane per row of an item");
     __shared__ R zsh[WAVES * CM_RB * 2 * NSX];
     R *zrow = zsh + (threadIdx.x >> 6) * (CM_RB * 2 * NSX);
-    const int64_t wave_id = (blockIdx.x * (int64_t)TPB + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)gridDim.x * TPB) >> 6;
-    for (int64_t it = wave_id; it < items; it += nwaves) {
+    static_assert(WAVES == COL_WAVES, "an item is a workgroup's");
+    __shared__ R csh[SHARE ? WAVES - 1 : 1][SHARE ? 3 * CM_CW : 1][64];  // the other wavefronts' column sums, for the first
+    const int wave = threadIdx.x >> 6;
+    const int64_t first = SHARE ? blockIdx.x : (blockIdx.x * (int64_t)TPB + threadIdx.x) >> 6;
+    const int64_t step = SHARE ? gridDim.x : ((int64_t)gridDim.x * TPB) >> 6;
+    for (int64_t it = first; it < items; it += step) {
         const int64_t rb = it / strips, sg = it - rb * strips;
-        const int64_t m0 = rb * rows, m1 = m0 + rows < M ? m0 + rows : M;
+        const int64_t m0 = (SHARE ? rb * WAVES + wave : rb) * rows, m1 = m0 + rows < M ? m0 + rows : M;
         const int64_t kb = sg * (64 * CM_CW) + lane;
         R ce[CM_CW], ca0[CM_CW], ca1[CM_CW];
 #pragma unroll
@@ -390,11 +395,33 @@ __device__ __forceinline__ void row_pass_cm(const LayerDev &L, int flags, R (&ch
                 atomic_add128_n<2 * NS>(cell, val, ok);
             }
         }
+        if constexpr (SHARE) {
+            if (wave > 0) {
+#pragma unroll
+                for (int c = 0; c < CM_CW; c++) {
+                    csh[wave - 1][3 * c][lane] = ce[c];
+                    csh[wave - 1][3 * c + 1][lane] = ca0[c];
+                    csh[wave - 1][3 * c + 2][lane] = ca1[c];
+                }
+            }
+            __syncthreads();
+            if (wave == 0) {
+#pragma unroll
+                for (int c = 0; c < CM_CW; c++)
+#pragma unroll
+                    for (int w = 0; w < WAVES - 1; w++) {
+                        ce[c] = add(ce[c], csh[w][3 * c][lane]);
+                        ca0[c] = add(ca0[c], csh[w][3 * c + 1][lane]);
+                        ca1[c] = add(ca1[c], csh[w][3 * c + 2][lane]);
+                    }
+            }
+        }
 #pragma unroll
         for (int c = 0; c < CM_CW; c++) {
             const int64_t k = kb + 64 * c;
-            if (k < K) add_cells<3>(P<R>(L.cvec), {o.Uc, o.tBc0, o.tBc1}, k, {ce[c], ca0[c], ca1[c]});
+            if (k < K && (!SHARE || wave == 0)) add_cells<3>(P<R>(L.cvec), {o.Uc, o.tBc0, o.tBc1}, k, {ce[c], ca0[c], ca1[c]});
         }
+        if constexpr (SHARE) __syncthreads();
     }
 }
 
@@ -425,13 +452,13 @@ __global__ __launch_bounds__(TPB) void k_row_pass_e(const LayerDev *__restrict__
 // Three workgroups per compute unit (at most 168 registers) for the 128-bit
 // single-output variant, the classifier's: the pass is bound by HBM and a
 // third wavefront per SIMD keeps more loads in flight.
-template <class R, int NS>
+template <class R, int NS, bool SHARE>
 __global__ __launch_bounds__(TPB, (sizeof(R) == 16 && NS == 1) ? 3 : 1) void k_row_pass_cm(
     const LayerDev *__restrict__ Ls, int flags) {
     const LayerDev &L = Ls[blockIdx.y];
-    if (row_variant(L.N) != NS || !L.cm) return;
+    if (row_variant(L.N) != NS || !L.cm || (bool)L.cm_share != SHARE) return;
     R chk[3] = {Ring<R>::zero(), Ring<R>::zero(), Ring<R>::zero()};
-    row_pass_cm<R, NS>(L, flags, chk);
+    row_pass_cm<R, NS, SHARE>(L, flags, chk);
     if (flags & F_CHECK)
         wave_accumulate_limbs<3>(chk, rp_cells<R>(L) + 12 * (((blockIdx.x * TPB + threadIdx.x) >> 6) % RP_COPIES));
 }
@@ -445,11 +472,15 @@ void launch_row_variants(const dim3 &g, const LayerDev *L, int flags, int varian
     if (variants & (1 << 4)) hipLaunchKernelGGL((k_row_pass<R, 4>), g, b, 0, st, L, flags);
     if (variants & (1 << 8)) hipLaunchKernelGGL((k_row_pass<R, SKINNY_MAX_N>), g, b, 0, st, L, flags);
     if (variants & (1 << VARIANT_E)) hipLaunchKernelGGL((k_row_pass_e<R>), g, b, 0, st, L, flags);
-    if (variants & (1 << (VARIANT_CM + 0))) hipLaunchKernelGGL((k_row_pass_cm<R, 0>), g, b, 0, st, L, flags);
-    if (variants & (1 << (VARIANT_CM + 1))) hipLaunchKernelGGL((k_row_pass_cm<R, 1>), g, b, 0, st, L, flags);
-    if (variants & (1 << (VARIANT_CM + 2))) hipLaunchKernelGGL((k_row_pass_cm<R, 2>), g, b, 0, st, L, flags);
-    if (variants & (1 << (VARIANT_CM + 4))) hipLaunchKernelGGL((k_row_pass_cm<R, 4>), g, b, 0, st, L, flags);
-    if (variants & (1 << (VARIANT_CM + 8))) hipLaunchKernelGGL((k_row_pass_cm<R, SKINNY_MAX_N>), g, b, 0, st, L, flags);
+#define LAUNCH_CM(v)                                                                                                       \
+    if (variants & (1 << (VARIANT_CM + cm_index(v)))) hipLaunchKernelGGL((k_row_pass_cm<R, v, false>), g, b, 0, st, L, flags); \
+    if (variants & (1 << (VARIANT_CM_SHARED + cm_index(v)))) hipLaunchKernelGGL((k_row_pass_cm<R, v, true>), g, b, 0, st, L, flags);
+    LAUNCH_CM(0)
+    LAUNCH_CM(1)
+    LAUNCH_CM(2)
+    LAUNCH_CM(4)
+    LAUNCH_CM(8)
+#undef LAUNCH_CM
 }
 
 hipError_t launch_row_pass(int eb, const LayerDev *L, int n, int flags, int64_t max_items, int variants, hipStream_t st) {
@@ -490,6 +521,7 @@ hipError_t launch_post(int eb, const LayerDev *L, int n, int flags, int64_t max_
 // k_compact_final adds [tC^c]_p and [Delta]_p (E^c U).
 template <class R>
 __global__ __launch_bounds__(TPB) void k_col_tag(const LayerDev *__restrict__ Ls) {
+    __shared__ R col[3][COL_WAVES][64];
     const LayerDev &L = Ls[blockIdx.y];
     if (!L.cm) return;
     const int64_t N = L.N;
@@ -504,11 +536,11 @@ __global__ __launch_bounds__(TPB) void k_col_tag(const LayerDev *__restrict__ Ls
         v[2] = mad(mad(v[2], ec, ld(P<R>(L.tB[1]), e)), ld(cv + o.tBc1, k), u);
     };
     auto done = [&](int64_t n, R (&v)[3]) { add_cells<3>(cv, {o.EUc, o.tZc0, o.tZc1}, n, v); };
-    col_sweep<R, 3>(hw_grid(), L.K, N, elem, done);
+    col_sweep<R, 3>(hw_grid(), L.K, N, col, elem, done);
 }
 
 hipError_t launch_col_tag(int eb, const LayerDev *L, int n, int64_t max_items, hipStream_t st) {
-    LAUNCH_RING(eb, k_col_tag, dim3(grid_items(max_items), n), dim3(TPB), st, L);
+    LAUNCH_RING(eb, k_col_tag, dim3(grid_items(max_items * WAVES), n), dim3(TPB), st, L);
     return hipGetLastError();
 }
 

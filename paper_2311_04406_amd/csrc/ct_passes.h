@@ -236,6 +236,7 @@ __device__ __forceinline__ void truncate_out(const LayerDev &L, int64_t e, R D) 
 template <class R>
 __device__ __forceinline__ void post_body(const LayerDev *__restrict__ Ls, int flags, const Grid &g) {
     __shared__ R sh[3 * WAVES];
+    __shared__ R col[5][COL_WAVES][64];
     const LayerDev &L = Ls[g.y];
     const int64_t M = L.M, N = L.N;
     const bool check = flags & F_CHECK, compact = flags & F_COMPACT;
@@ -264,7 +265,7 @@ __device__ __forceinline__ void post_body(const LayerDev *__restrict__ Ls, int f
         auto done = [&](int64_t i, R (&v)[5]) {
             add_cells<5>(P<R>(L.cvec), {o.Dc, o.tRc0, o.tRc1, o.tCc0, o.tCc1}, i, v);
         };
-        if (cm) col_sweep<R, 5>(g, M, N, elem, done);
+        if (cm) col_sweep<R, 5>(g, M, N, col, elem, done);
         else row_sweep<R, 5>(g, M, N, elem, done);
     } else {
         const int64_t n = M * N;

@@ -164,49 +164,45 @@ __device__ __forceinline__ void row_sweep(const Grid &g, int64_t rows, int64_t N
 }
 
 // Column sweep over an R x N matrix (sums down the columns), the mirror of
-// row_sweep.  N <= 32: a wavefront covers 64 / G rows of G = pow2ceil(N)
-// columns at a time (coalesced), takes rb such row groups per item and
-// reduces over the lanes of one column; wider matrices give each lane a
-// column and each item 64 columns of rb rows (rb = col_sweep_rb(rows)).
+// row_sweep, by the workgroups of grid g.  N <= 32: a wavefront covers 64 / G
+// rows of G = pow2ceil(N) columns at a time (coalesced), takes rb such row
+// groups per item and reduces over the lanes of one column; wider matrices
+// give each lane a column and each wavefront rb rows of 64 columns.  The four
+// wavefronts of an item take neighbouring rows and add their sums through sh.
 // elem(r, c, v) accumulates into the NV column sums v; col_done(c, v)
 // receives each item's sums and must add them atomically.
 template <class R, int NV, typename Elem, typename ColDone>
-__device__ __forceinline__ void col_sweep(const Grid &g, int64_t rows, int64_t N, Elem elem, ColDone col_done) {
-    const int lane = threadIdx.x & 63;
-    const int64_t wave_id = ((int64_t)g.x * TPB + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)g.nx * TPB) >> 6;
-    const int64_t rb = col_sweep_rb(rows, N);
-    if (N <= 32) {
-        const int G = (int)col_sweep_group(N);
-        const int rpw = 64 / G, c = lane % G;
-        const int64_t per = (int64_t)rpw * rb, items = (rows + per - 1) / per;
-        for (int64_t it = wave_id; it < items; it += nwaves) {
-            R v[NV];
+__device__ __forceinline__ void col_sweep(const Grid &g, int64_t rows, int64_t N, R (*sh)[COL_WAVES][64], Elem elem,
+                                          ColDone col_done) {
+    static_assert(WAVES == COL_WAVES, "an item is a workgroup's");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t rb = col_sweep_rb(rows, N), items = col_sweep_items(rows, N);
+    const bool narrow = N <= 32;
+    const int G = narrow ? (int)col_sweep_group(N) : 64, rpw = 64 / G;
+    const int64_t chunks = narrow ? 1 : (N + 63) / 64, per = rpw * rb;
+    for (int64_t it = g.x; it < items; it += g.nx) {
+        const int64_t b = narrow ? it : it / chunks, c = narrow ? lane % G : (it - b * chunks) * 64 + lane;
+        const int64_t r0 = (b * WAVES + wave) * per, r1 = r0 + per < rows ? r0 + per : rows;
+        R v[NV];
 #pragma unroll
-            for (int i = 0; i < NV; i++) v[i] = Ring<R>::zero();
-            for (int64_t j = 0; j < rb; j++) {
-                const int64_t r = it * per + (int64_t)j * rpw + lane / G;
-                if (r < rows && c < N) elem(r, (int64_t)c, v);
-            }
-            for (int m = 32; m >= G; m >>= 1) {
+        for (int i = 0; i < NV; i++) v[i] = Ring<R>::zero();
+        if (c < N)
+            for (int64_t r = r0 + lane / G; r < r1; r += rpw) elem(r, c, v);
+        for (int m = 32; m >= G; m >>= 1) {
 #pragma unroll
-                for (int i = 0; i < NV; i++) v[i] = add(v[i], shfl_xor128(v[i], m));
-            }
-            if (lane < G && c < N) col_done((int64_t)c, v);
+            for (int i = 0; i < NV; i++) v[i] = add(v[i], shfl_xor128(v[i], m));
         }
-    } else {
-        const int64_t chunks = (N + 63) / 64, items = chunks * ((rows + rb - 1) / rb);
-        for (int64_t it = wave_id; it < items; it += nwaves) {
-            const int64_t b = it / chunks, c = (it - b * chunks) * 64 + lane;
-            const int64_t r0 = b * rb, r1 = r0 + rb < rows ? r0 + rb : rows;
-            R v[NV];
 #pragma unroll
-            for (int i = 0; i < NV; i++) v[i] = Ring<R>::zero();
-            if (c < N) {
-                for (int64_t r = r0; r < r1; r++) elem(r, c, v);
-                col_done(c, v);
-            }
+        for (int i = 0; i < NV; i++) sh[i][wave][lane] = v[i];
+        __syncthreads();
+        if (wave == 0 && lane < G && c < N) {
+#pragma unroll
+            for (int i = 0; i < NV; i++)
+#pragma unroll
+                for (int w = 1; w < WAVES; w++) v[i] = add(v[i], sh[i][w][lane]);
+            col_done(c, v);
         }
+        __syncthreads();
     }
 }
 

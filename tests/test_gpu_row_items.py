@@ -1,6 +1,7 @@
 """The pass over M x K where the cut of a layer into work items changes (rows
 shorter than, at and past one segment; few and many rows; row blocks with a
-remainder when compressing along M), against the oracle, bit-exact."""
+remainder when compressing along M) and the column sweeps, against the oracle,
+bit-exact."""
 import pytest
 import torch
 
@@ -20,8 +21,10 @@ class Spec:
 
 # along N: segments of 128 (few rows), 256 and 512 (around ROW_ITEMS = 512 items), 1024
 ALONG_N = [(1, 127, 9), (3, 129, 1), (255, 257, 9), (256, 513, 2), (257, 300, 4), (511, 1025, 9), (513, 1000, 8)]
-# along M: blocks of 2 rows, of 4 to 16 and of 32 (around CM_ITEMS = 1024 items), a remainder of one row
-ALONG_M = [(3, 65, 9), (65, 513, 3), (517, 1025, 9), (1031, 515, 2), (2051, 770, 10), (8195, 260, 1)]
+# along M: 2, 4 to 16 and 32 rows a wavefront, shared by workgroup or not (2051 x 4100 x 1, 1900 x 1100 x 5), a
+# remainder of one row; column sweeps of several row groups per wavefront (K > 2048, M > 2048)
+ALONG_M = [(3, 65, 9), (65, 513, 3), (517, 1025, 9), (1031, 515, 2), (2051, 770, 10), (8195, 260, 1), (8300, 65, 3),
+           (2051, 4100, 1), (1900, 1100, 5), (33, 2500, 40), (2600, 40, 40)]
 CASES = ([(Spec(*s), p) for s in ALONG_N for p in (2, 3)] + [(Spec(*s, compress=1), 2) for s in ALONG_M])
 
 
