@@ -223,7 +223,8 @@ __device__ __forceinline__ void store_tile(uint8_t *tile, int off, const uint32_
     __syncthreads();
     CT_GLOBAL ct_u32x4 *d = global_ptr<ct_u32x4>(dst);
 #pragma unroll
-    for (int i = 0; i < OPB / 16 / 256; i++) d[i * 256 + threadIdx.x] = reinterpret_cast<const ct_u32x4 *>(tile)[i * 256 + threadIdx.x];
+    for (int i = 0; i < OPB / 16 / 256; i++)
+        __builtin_nontemporal_store(reinterpret_cast<const ct_u32x4 *>(tile)[i * 256 + threadIdx.x], d + i * 256 + threadIdx.x);
     __syncthreads();
 }
 

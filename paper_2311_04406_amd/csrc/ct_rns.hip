@@ -123,7 +123,9 @@ __device__ __forceinline__ uint32_t pack4(uint32_t a, uint32_t b, uint32_t c, ui
 // than 1 / m: |S - m q| <= 127 for every odd m <= 253), and q times (256 - m)
 // added to the bits leaves S - m q in the low byte.  Four moduli at a time: 16
 // bytes of theirs take few registers, which leaves room for the loads of the
-// next operand.
+// next operand.  The planes go past the caches: a launch writes far more than
+// they hold, and the products, which read them next, ran 2.72 ms on twelve
+// encoders with ordinary stores and 2.25 with these (the openings 3% longer).
 __device__ __forceinline__ void convert(const u128 (&x)[16], int side, uint8_t *dst, int64_t plane) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -152,7 +154,8 @@ __device__ __forceinline__ void convert(const u128 (&x)[16], int side, uint8_t *
         }
 #pragma unroll
         for (int r = 0; r < 4; r++)
-            *global_ptr<ct_u32x4>(dst + (int64_t)(4 * g + r) * plane) = ct_u32x4{out[r][0], out[r][1], out[r][2], out[r][3]};
+            __builtin_nontemporal_store(ct_u32x4{out[r][0], out[r][1], out[r][2], out[r][3]},
+                                        global_ptr<ct_u32x4>(dst + (int64_t)(4 * g + r) * plane));
     }
 }
 
@@ -647,7 +650,8 @@ __device__ __forceinline__ void rns_tile(const RnsProb &P, int q, int tm, int tn
                     }
                     w[d] = pack4(b[0], b[1], b[2], b[3]);
                 }
-                if (rm0 + i < mb && rn0 + j < nb) *global_ptr<ct_u32x4>(res + tile_off(o, i, j)) = ct_u32x4{w[0], w[1], w[2], w[3]};
+                if (rm0 + i < mb && rn0 + j < nb)
+                    __builtin_nontemporal_store(ct_u32x4{w[0], w[1], w[2], w[3]}, global_ptr<ct_u32x4>(res + tile_off(o, i, j)));
             }
 }
 
