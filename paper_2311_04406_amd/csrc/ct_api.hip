@@ -427,10 +427,12 @@ RnsShape rns_online_shape(const ct_layer_desc &d, int np, bool compact) {
     s.M = d.M; s.K = d.K; s.N = d.N;
     s.nl = s.nr = compact ? np + 1 : 2 * np + 1;
     s.outs = compact ? np : 2 * np;
+    if (np > 2 && compact) s.rate = 0.85e5;  // an encoder of three parties: 1314 us by digits, 1340 by residues
     if (np == 2 && compact) {
         const bool cm = CT_COMPRESS_ALONG_M(d.M, d.N, d.compress);
-        // the one pass that opens, compresses and converts; convolutions are converted from memory on both paths
-        s.rate = d.conv_c != 0 ? 1.0e5 : cm ? s.rate : 1.38e5;
+        // one pass opens, compresses and converts, but along M only the digit path's (595 us for a drawn batch of
+        // such layers by digits, 650 by residues where 1.0e5 sent them there)
+        if (d.conv_c == 0) s.rate = cm ? 0.76e5 : 1.38e5;
         // only layers compressed along M open U apart from its conversion here and together with it there
         if (d.conv_c == 0 && cm) s.refetch = 48.0 * d.K * d.N;
     }
@@ -446,18 +448,22 @@ bool rns_alloc(RnsMemory &m) {
     return false;
 }
 
-// take[l]: layer l's online products go through residues.
+// take[l]: layer l's online products go through residues.  A lane without
+// another to lend it a stream is the one beside the skinny layers'.
 std::vector<char> rns_layers(const ct_ctx *c, const Lane &ln, ct_mode mode, const ct_layer_desc *L, int n) {
     std::vector<char> take(n, 0);
     if (!rns_allowed(c) || !ln.rns || ln.rns->bytes <= 0) return take;
     std::vector<RnsShape> s;
     std::vector<int> at;
+    bool skinny = !ln.aux;
     for (int l = 0; l < n; l++)
         if (L[l].N > SKINNY_MAX_N) {
             s.push_back(rns_online_shape(L[l], c->np, mode == CT_MODE_COMPACT));
             at.push_back(l);
+        } else {
+            skinny = true;
         }
-    const std::vector<char> t = rns_choose(s, ln.rns->bytes);
+    const std::vector<char> t = rns_choose(s, ln.rns->bytes, skinny);
     int64_t need = 0;
     for (size_t i = 0; i < at.size(); i++)
         if (t[i]) need += rns_align(s[i].bytes(s[i].chunk_len(1)));
@@ -1301,7 +1307,7 @@ ct_status run_check(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_desc *L, c
     if (c->np > 2) {
         LAUNCH(c, ln, ST_ZERO_ACC, launch_np_zero(c->eb, ln.layers_dev, n, 2, 0, ln.stream));
         LAUNCH(c, ln, ST_CHECK_BATCH,
-               launch_np_check_batch(c->eb, ln.layers_dev, n, mask, std::max({sz.mk, sz.nr, sz.mn}), ln.stream));
+               launch_np_check_batch(c->eb, c->np, ln.layers_dev, n, mask, std::max({sz.mk, sz.nr, sz.mn}), ln.stream));
         if (compact) LAUNCH(c, ln, ST_CHECK_COMPACT, launch_np_check_compact(c->eb, ln.layers_dev, n, ln.stream));
         LAUNCH(c, ln, ST_FINALIZE, launch_np_finalize(c->eb, ln.layers_dev, n, out_dev, ln.stream));
         return CT_OK;

@@ -423,7 +423,7 @@ hipError_t launch_np_row_pass(int eb, int np, const LayerDev *L, int n, int flag
                               hipStream_t st);
 hipError_t launch_np_gemv(int eb, const LayerDev *L, int n, int64_t max_items, hipStream_t st);
 hipError_t launch_np_compact_final(int eb, const LayerDev *L, int n, int flags, hipStream_t st);
-hipError_t launch_np_check_batch(int eb, const LayerDev *L, int n, int which_mask, int64_t max_elems, hipStream_t st);
+hipError_t launch_np_check_batch(int eb, int np, const LayerDev *L, int n, int which_mask, int64_t max_elems, hipStream_t st);
 hipError_t launch_np_check_compact(int eb, const LayerDev *L, int n, hipStream_t st);
 hipError_t launch_np_finalize(int eb, const LayerDev *L, int n, ct_check_result *out, hipStream_t st);
 hipError_t launch_check_batch(int eb, const LayerDev *L, int n, int which, int64_t max_elems, hipStream_t st);

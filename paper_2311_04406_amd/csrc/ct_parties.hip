@@ -618,11 +618,12 @@ hipError_t launch_np_compact_final(int eb, const LayerDev *L, int n, int flags, 
 // ---------------------------------------------------------------- checks
 // Standalone Pi_BatchRec tag check (Fig. 1) of W = P - Q: y = layer * 3 + which,
 // which = 0: E (X, A), 1: U (Y, B), 2: D (R, Z).
-template <class R>
+// (NP = the parties: a party's loads do not wait for the one before.)
+template <class R, int NP>
 __global__ __launch_bounds__(TPB) void k_np_check_batch(const LayerDev *__restrict__ Ls, int which_mask) {
     __shared__ R sh[ACC_W * WAVES];
     const LayerDev &L = Ls[blockIdx.y / 3];
-    const int which = blockIdx.y % 3, np = L.np;
+    const int which = blockIdx.y % 3;
     if (!((which_mask >> which) & 1)) return;
     int64_t n;
     u128 *const *tP;
@@ -643,17 +644,23 @@ __global__ __launch_bounds__(TPB) void k_np_check_batch(const LayerDev *__restri
     for (int64_t e = blockIdx.x * (int64_t)TPB + threadIdx.x; e < n; e += (int64_t)gridDim.x * TPB) {
         const uint64_t c = Ring<R>::mod_s(sdraw(key, (uint64_t)e));
 #pragma unroll
-        for (int p = 0; p < MAXP; p++)
-            if (p < np) v[p] = mad64(v[p], sub(ld(P<R>(tP[p]), e), ld(P<R>(tQ[p]), e)), c);
+        for (int p = 0; p < NP; p++) v[p] = mad64(v[p], sub(ld(P<R>(tP[p]), e), ld(P<R>(tQ[p]), e)), c);
         v[MAXP] = mad64(v[MAXP], ld(W, e), c);
     }
     block_accumulate<ACC_W>(v, sh, P<R>(L.acc) + which * ACC_W);
 }
 
-hipError_t launch_np_check_batch(int eb, const LayerDev *L, int n, int which_mask, int64_t max_elems, hipStream_t st) {
-    int g = grid_for(max_elems);
-    if (g > 2048) g = 2048;
-    LAUNCH_RING(eb, k_np_check_batch, dim3(g, 3 * n), dim3(TPB), st, L, which_mask);
+template <class R>
+void launch_np_check_parties(int np, const dim3 &g, const LayerDev *L, int which_mask, hipStream_t st) {
+    if (np == 3) hipLaunchKernelGGL((k_np_check_batch<R, 3>), g, dim3(TPB), 0, st, L, which_mask);
+    else if (np == 4) hipLaunchKernelGGL((k_np_check_batch<R, 4>), g, dim3(TPB), 0, st, L, which_mask);
+    else hipLaunchKernelGGL((k_np_check_batch<R, 5>), g, dim3(TPB), 0, st, L, which_mask);
+}
+
+hipError_t launch_np_check_batch(int eb, int np, const LayerDev *L, int n, int which_mask, int64_t max_elems, hipStream_t st) {
+    const dim3 g(std::min(grid_for(max_elems), 2048), 3 * n);
+    if (eb == 8) launch_np_check_parties<r64>(np, g, L, which_mask, st);
+    else launch_np_check_parties<u128>(np, g, L, which_mask, st);
     return hipGetLastError();
 }
 

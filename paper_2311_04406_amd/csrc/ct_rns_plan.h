@@ -23,7 +23,7 @@ constexpr int RNS_MAX_CHUNKS = 64;
 struct RnsShape {
     int64_t M = 0, K = 0, N = 0;
     int nl = 0, nr = 0, outs = 0, segs = 2;
-    double rate = 0.76e5;  // operand elements converted and read back per microsecond, beyond the digit path's
+    double rate = 1.0e5;  // operand elements converted and read back per microsecond, beyond the digit path's
     double refetch = 0;    // bytes that the conversion reads and the digit path does not
     int64_t res_bytes() const { return (int64_t)outs * RNS_N * rns_blocks(M) * rns_blocks(N) * 1024; }
     int64_t bytes(int64_t kc) const {
@@ -43,10 +43,10 @@ struct RnsShape {
     // 136 against 36 matrix products per multiply-add (1.2e15 digit and 0.9e15
     // residue products a second), against the 20 bytes more per operand element
     // and the residues of the outputs.  Fitted to 78 single layers (2 to 4
-    // parties, both protocols) and 15 batches timed on either path; a layer of
-    // two parties and CompactTag gains, for instance, 67 us of 352 at
-    // 128 x 768 x 2304 and 1601 of 3679 at 2048^3, and loses 264 of 1174 at
-    // 64 x 4096 x 4096: the sign changes near M N / (M + N) = 80.
+    // parties, both protocols) and 60 batches timed on either path.  With two
+    // parties and CompactTag a layer of 2048^3 takes 2061 us by residues and 3661
+    // by digits, 256 x 768 x 768 201 and 211, 64 x 4096 x 4096 1438 and 1224; an
+    // encoder in SPDZ2k 1152 and 1191.  The sign changes near M N / (M + N) = 80.
     double saves_us() const {
         const double pm = 32.0 * rns_blocks(M), pn = 32.0 * rns_blocks(N);
         return digits_us() - (double)outs * segs * pm * K * pn * (36 / 0.9e9) - (nl * pm + nr * pn) * K / rate - refetch / 5.5e6 -
@@ -58,10 +58,15 @@ struct RnsShape {
 // path.  Each path brings launches of its own, tens of microseconds on a small
 // call, so a few layers on the slower side follow the others (up to 100 us of
 // digit products), and a call that would gain less than 18 us, or less than
-// 80 us and keep both paths for it, stays with digits.
-inline std::vector<char> rns_choose(const std::vector<RnsShape> &s, int64_t cap) {
+// 80 us and keep both paths for it, stays with digits.  So does one that would
+// gain little for its size: a fifth below 300 us of digit products (seven
+// layers with 200 us of them took 457 us by digits and 476 by residues, at 17%),
+// a tenth above; and a quarter of any beside skinny layers, whose pass, bound by
+// HBM, overlaps with the digit products but not with the conversions (1176 us
+// and 1217).
+inline std::vector<char> rns_choose(const std::vector<RnsShape> &s, int64_t cap, bool skinny) {
     std::vector<char> take(s.size(), 0);
-    double gain = 0, rest_us = 0, rest_loss = 0;
+    double gain = 0, taken_us = 0, rest_us = 0, rest_loss = 0;
     bool others = false, able = true;
     for (size_t i = 0; i < s.size(); i++) {
         const double save = s[i].saves_us();
@@ -69,6 +74,7 @@ inline std::vector<char> rns_choose(const std::vector<RnsShape> &s, int64_t cap)
         if (can && save > 4) {
             take[i] = 1;
             gain += save;
+            taken_us += s[i].digits_us();
         } else {
             others = true;
             able &= can;
@@ -79,9 +85,11 @@ inline std::vector<char> rns_choose(const std::vector<RnsShape> &s, int64_t cap)
     if (others && able && rest_us < 100 && gain > rest_loss) {
         take.assign(s.size(), 1);
         gain -= rest_loss;
+        taken_us += rest_us;
         others = false;
     }
-    if (gain < (others ? 80 : 18)) take.assign(s.size(), 0);
+    const double part = skinny ? 0.25 : taken_us < 300 ? 0.2 : 0.1;
+    if (gain < (others ? 80 : 18) || gain < part * taken_us) take.assign(s.size(), 0);
     return take;
 }
 

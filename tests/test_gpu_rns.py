@@ -33,9 +33,9 @@ def staged_run(ctx, mode, layers, out):
 # M, N: one past, one short of and at multiples of 32-row blocks and 128-row
 # tiles; K: ragged slices of 64, one to several chunks
 CASES = [(Spec(449, 1025, 481), 2, 1), (Spec(512, 640, 512), 2, 1), (Spec(415, 1100, 415), 2, 0),
-         (Spec(545, 1100, 513, f=13, compress=1), 2, 1), (Spec(481, 897, 484, conv=(897, 22, 22, 1, 1, 0)), 2, 1),
+         (Spec(833, 1100, 801, f=13, compress=1), 2, 1), (Spec(513, 1001, 484, conv=(1001, 22, 22, 1, 1, 0)), 2, 1),
          (Spec(385, 1152, 784, conv=(128, 28, 28, 3, 1, 1)), 2, 1),
-         (Spec(417, 1300, 450), 3, 1), (Spec(353, 900, 448), 4, 0), (Spec(481, 700, 450), 5, 1)]
+         (Spec(641, 900, 610), 3, 1), (Spec(353, 900, 448), 4, 0), (Spec(577, 700, 610), 5, 1)]
 
 
 @pytest.mark.parametrize("spec,parties,mode", CASES, ids=[f"{s.name}-p{p}-m{m}" for s, p, m in CASES])
