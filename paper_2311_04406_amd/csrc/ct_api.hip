@@ -566,13 +566,14 @@ int64_t gemm_length(const std::vector<GemmProb> &probs, int num_cus, int wg, int
 
 // Whether the wavefronts of a workgroup share the K slices of one output tile
 // (WS_K4), and into how many slices per workgroup K is then split: for launches
-// of fewer than two 64 x 64 tiles per compute unit (k = s = 32, with a quarter
+// of fewer than one 64 x 64 tile per compute unit (k = s = 32, with a quarter
 // of the products per fragment: half a tile) whose configuration is left to the library, if it is the shorter way by gemm_length.  Larger launches
 // keep every compute unit busy without, and read half as many fragments.
 // Measured with the launch for constant terms, us before and after:
 // 64 x 128 x 32 27.6 and 15.7, 256 x 256 x 256 39.8 and 26.0, 96 x 1024 x 1024
 // 93.7 and 57.7, 130 x 4608 x 300 131.7 and 109.9; the other way round for
-// 512 x 64 x 512 (24.7 and 32.5), which the rule leaves as it was.
+// 512 x 64 x 512 (24.7 and 32.5), which the rule leaves as it was, and for two
+// batches of 272 and 396 tiles with short K (72 and 84, 60 and 88).
 int64_t k4_target(const std::vector<GemmProb> &probs, int num_cus, const GemmTuning &tu, int eb) {
     if (tu.tile != CT_TILE_AUTO || tu.split_target != 0) return 0;
     int64_t tiles = 0, steps = 0, most = 0;
@@ -582,7 +583,7 @@ int64_t k4_target(const std::vector<GemmProb> &probs, int num_cus, const GemmTun
         steps += t * n;
         most = std::max(most, n);
     }
-    if (tiles >= (eb == 8 ? num_cus / 2 : 2 * num_cus)) return 0;
+    if (tiles >= (eb == 8 ? num_cus / 2 : num_cus)) return 0;
     int64_t best = gemm_length(probs, num_cus, 64, default_target(steps, num_cus), 1), choice = 0;
     for (int64_t t = 32; ; t += t / 8) {  // 8 slices a wavefront and more
         const int64_t target = std::min<int64_t>(t, MAX_STEPS_PER_SPLIT), len = gemm_length(probs, num_cus, 32, target, 4);
@@ -1156,7 +1157,8 @@ ct_status prepare_online(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_desc 
     P.max_row_items = sz.row_items;
     P.max_mn = sz.mn;
     P.max_mn_items = sz.mn_items;
-    P.any_cm = compact && sz.cm;
+    P.any_cm = P.all_cm = compact && sz.cm;
+    for (int l = 0; l < n; l++) P.all_cm &= ln.layers_host[l].cm != 0;
     P.max_col_tag = sz.col_tag;
     P.any_conv_n = compact && sz.conv_n;
     P.max_conv_items = sz.conv_items;
@@ -1238,7 +1240,7 @@ ct_status enqueue_online(ct_ctx *c, Lane &ln, const OnlineLaunch &P) {
     ct_status s = products();
     const ct_status j = join_products(c, ln, over);  // also on failure, so that the streams stay joined
     if (s != CT_OK || (s = j) != CT_OK) return s;
-    LAUNCH(c, ln, ST_POST, launch_post(c->eb, ln.layers_dev, n, P.flags, P.max_mn_items, ln.stream));
+    LAUNCH(c, ln, ST_POST, launch_post(c->eb, ln.layers_dev, n, P.flags, P.max_mn_items, P.any_cm, P.all_cm, ln.stream));
     if (P.compact) LAUNCH(c, ln, ST_COMPACT_FINAL, launch_compact_final(c->eb, ln.layers_dev, n, P.flags, ln.stream));
     if (P.check) LAUNCH(c, ln, ST_FINALIZE, launch_finalize(c->eb, ln.layers_dev, n, P.out_dev, ln.stream));
     return CT_OK;

@@ -125,7 +125,8 @@ struct OnlineLaunch {
     int n = 0, nm = 0, njobs = 0, pack_tiles = 0, total_tiles = 0, variants = 0, flags = 0, zero_what = 0;
     int open_tiles = 0;       // k_open_pack tiles of the largest fused layer
     bool any_open_u = false;  // a layer that k_open_u opens (not fused)
-    bool any_accum = false, compact = false, check = false, any_cm = false, any_conv_n = false;
+    bool any_accum = false, compact = false, check = false, any_cm = false, all_cm = false,
+         any_conv_n = false;
     ct_mode mode = CT_MODE_COMPACT;
     GemmTuning tu;
     RnsPlan rns;

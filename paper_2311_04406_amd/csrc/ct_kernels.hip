@@ -24,7 +24,9 @@
 // K x N).  Convolution layers open U on their input's elements in k_open_u
 // and compress their implicit im2col matrices in k_conv_compress.  Two-party
 // matrix-core layers that are not convolutions open U in k_open_pack
-// (ct_gemm.hip), which also writes their right operands' digit tiles.
+// (ct_gemm.hip), which also writes their right operands' digit tiles; those
+// whose products go through residues (FO_RNS) open E and U in ct_rns.hip and
+// take k_row_pass_e.
 //
 // Every kernel serves all layers of a call: grid dimension y indexes layers
 // (and sub-objects), dimension x strides over that layer's work.  Cross-
@@ -507,9 +509,16 @@ template <class R>
 __global__ __launch_bounds__(TPB) void k_post(const LayerDev *__restrict__ Ls, int flags) {
     post_body<R>(Ls, flags, hw_grid());
 }
+template <class R>
+__global__ __launch_bounds__(TPB) void k_post_cm(const LayerDev *__restrict__ Ls, int flags) {
+    post_body<R, true>(Ls, flags, hw_grid());
+}
 
-hipError_t launch_post(int eb, const LayerDev *L, int n, int flags, int64_t max_items, hipStream_t st) {
-    LAUNCH_RING(eb, k_post, dim3(grid_items(max_items), n), dim3(TPB), st, L, flags);
+hipError_t launch_post(int eb, const LayerDev *L, int n, int flags, int64_t max_items, bool any_cm, bool all_cm,
+                       hipStream_t st) {
+    const dim3 g(grid_items(max_items), n);
+    if (!all_cm) LAUNCH_RING(eb, k_post, g, dim3(TPB), st, L, flags);
+    if (any_cm) LAUNCH_RING(eb, k_post_cm, g, dim3(TPB), st, L, flags);
     return hipGetLastError();
 }
 
@@ -590,9 +599,9 @@ __global__ __launch_bounds__(TPB) void k_check_batch(const LayerDev *__restrict_
     R v[3] = {Ring<R>::zero(), Ring<R>::zero(), Ring<R>::zero()};
     for (int64_t e = blockIdx.x * (int64_t)TPB + threadIdx.x; e < n; e += (int64_t)gridDim.x * TPB) {
         const uint64_t c = Ring<R>::mod_s(sdraw(key, (uint64_t)e));
-        v[0] = mad64(v[0], sub(ld(tP0, e), ld(tQ0, e)), c);
-        v[1] = mad64(v[1], sub(ld(tP1, e), ld(tQ1, e)), c);
-        v[2] = mad64(v[2], ld(W, e), c);
+        v[0] = mad64(v[0], sub(ld_nt(tP0, e), ld_nt(tQ0, e)), c);
+        v[1] = mad64(v[1], sub(ld_nt(tP1, e), ld_nt(tQ1, e)), c);
+        v[2] = mad64(v[2], ld_nt(W, e), c);
     }
     block_accumulate<3>(v, sh, P<R>(L.acc) + 3 * which);
 }

@@ -235,17 +235,19 @@ __device__ __forceinline__ void truncate_out(const LayerDev &L, int64_t e, R D) 
     st(P<R>(L.tZf[1]), e, sub(ld(P<R>(L.tRf[1]), e), mul64(Ring<R>::small(L.delta[1]), df)));
 }
 
-template <class R>
+// CM: the layers compressed along M (the others take the kernel without the
+// column sums, whose registers cost it a wavefront per SIMD).
+template <class R, bool CM = false>
 __device__ __forceinline__ void post_body(const LayerDev *__restrict__ Ls, int flags, const Grid &g) {
     __shared__ R sh[3 * WAVES];
-    __shared__ R col[5][COL_WAVES][64];
+    __shared__ R col[CM ? 5 : 1][COL_WAVES][CM ? 64 : 1];
     const LayerDev &L = Ls[g.y];
+    if (((flags & F_COMPACT) && L.cm) != CM) return;
     const int64_t M = L.M, N = L.N;
     const bool check = flags & F_CHECK, compact = flags & F_COMPACT;
     const uint64_t kchi = L.key[K_CHI], kcd = L.key[K_CHI_D];
     R chk[3] = {Ring<R>::zero(), Ring<R>::zero(), Ring<R>::zero()};
     if (compact) {
-        const bool cm = L.cm;
         const CvecOff o = cvec_off(cvec_rows(L), L.K);
         auto elem = [&](int64_t r, int64_t c, R (&v)[5]) {
             const int64_t e = r * N + c;
@@ -256,7 +258,7 @@ __device__ __forceinline__ void post_body(const LayerDev *__restrict__ Ls, int f
             st(P<R>(L.tZ[0]), e, sub(tr0, mul64(D, L.delta[0])));
             st(P<R>(L.tZ[1]), e, sub(tr1, mul64(D, L.delta[1])));
             // combiner of the compressed index: the column (along N) or the row (along M)
-            const uint64_t x = Ring<R>::mod_s(sdraw(kchi, (uint64_t)(cm ? r : c)));
+            const uint64_t x = Ring<R>::mod_s(sdraw(kchi, (uint64_t)(CM ? r : c)));
             v[0] = mad64(v[0], D, x);
             v[1] = mad64(v[1], tr0, x);
             v[2] = mad64(v[2], tr1, x);
@@ -267,7 +269,7 @@ __device__ __forceinline__ void post_body(const LayerDev *__restrict__ Ls, int f
         auto done = [&](int64_t i, R (&v)[5]) {
             add_cells<5>(P<R>(L.cvec), {o.Dc, o.tRc0, o.tRc1, o.tCc0, o.tCc1}, i, v);
         };
-        if (cm) col_sweep<R, 5>(g, M, N, col, elem, done);
+        if constexpr (CM) col_sweep<R, 5>(g, M, N, col, elem, done);
         else row_sweep<R, 5>(g, M, N, elem, done);
     } else {
         const int64_t n = M * N;
