@@ -332,6 +332,7 @@ ct_status stage_layers(ct_ctx *c, Lane &ln, const ct_layer_desc *L, const ct_lay
     lane_place(ln, n, c->np);
     for (int l = 0; l < n; l++) {
         fill_layer(c, ln.acc_dev, L[l], B[l], l, ln.layers_host[l]);
+        ln.layers_host[l].uc = ln.uc_dev + (int64_t)l * RP_CELLS;
         ln.layers_host[l].out_index = out_index ? out_index[l] : l;
     }
     return CT_OK;
@@ -726,14 +727,15 @@ hipError_t lane_init(Lane &ln, hipStream_t stream, int max_layers, int np) {
 #define LANE_TRY(expr) \
     if ((err = (expr)) != hipSuccess) return err
     const int64_t tables = lane_place(ln, max_layers, np);  // sizes only: the blocks do not exist yet
-    const int64_t acc = sizeof(u128) * ACC_PER_LAYER * (int64_t)max_layers;
+    const int64_t uc = ln.rns ? sizeof(*ln.uc_dev) * RP_CELLS * (int64_t)max_layers : 0;
     const int64_t res = (sizeof(ct_check_result) * (int64_t)max_layers + 255) & ~(int64_t)255;
-    LANE_TRY(hipMalloc(&ln.dev, tables + acc + res + 64));
+    LANE_TRY(hipMalloc(&ln.dev, tables + uc + res + 64));
+    LANE_TRY(hipMalloc(&ln.acc_dev, sizeof(u128) * ACC_PER_LAYER * (int64_t)max_layers));  // of its own: see ACC_PER_LAYER
     LANE_TRY(hipHostMalloc(&ln.host, tables + res, hipHostMallocDefault));
     lane_place(ln, max_layers, np);
-    ln.acc_dev = reinterpret_cast<u128 *>(ln.dev + tables);
-    ln.res_dev = reinterpret_cast<ct_check_result *>(ln.dev + tables + acc);
-    ln.sync_dev = reinterpret_cast<uint32_t *>(ln.dev + tables + acc + res);
+    ln.uc_dev = reinterpret_cast<unsigned long long *>(ln.dev + tables);
+    ln.res_dev = reinterpret_cast<ct_check_result *>(ln.dev + tables + uc);
+    ln.sync_dev = reinterpret_cast<uint32_t *>(ln.dev + tables + uc + res);
     ln.res_host = reinterpret_cast<ct_check_result *>(ln.host + tables);
     LANE_TRY(hipEventCreateWithFlags(&ln.upload_done, hipEventDisableTiming));
     LANE_TRY(hipEventRecord(ln.upload_done, ln.stream));
@@ -747,6 +749,7 @@ void lane_free(Lane &ln) {
     for (hipEvent_t e : {ln.upload_done, ln.ev_ready, ln.ev_free[0], ln.ev_free[1], ln.ev_join})
         if (e) (void)hipEventDestroy(e);
     if (ln.dev) (void)hipFree(ln.dev);
+    if (ln.acc_dev) (void)hipFree(ln.acc_dev);
     if (ln.host) (void)hipHostFree(ln.host);
     ln = Lane();
 }

@@ -35,7 +35,7 @@ struct Lane {
     int max_layers = 0, max_probs = 0, max_jobs = 0;
     // One block on the device and one pinned.  They begin with the tables of the call at hand (lane_place): layer
     // records, product problems and packing jobs, then those of the other paths, at the same offsets in both, so that
-    // one copy uploads them all.  Behind the room for max_layers layers: check accumulators, results, counters.
+    // one copy uploads them all.  Behind the room for max_layers layers: copies of sums, results, counters.
     uint8_t *dev = nullptr, *host = nullptr;
     LayerDev *layers_dev = nullptr, *layers_host = nullptr;
     GemmProb *gemm_dev = nullptr, *gemm_host = nullptr;           // max_probs
@@ -46,7 +46,8 @@ struct Lane {
     RnsProb *rns_probs_dev = nullptr, *rns_probs_host = nullptr;  // max_probs
     // residue products: memory of the lane's context or plan (null: every product by digits; set before lane_init)
     RnsMemory *rns = nullptr;
-    u128 *acc_dev = nullptr;
+    u128 *acc_dev = nullptr;               // check accumulators, a block of their own
+    unsigned long long *uc_dev = nullptr;  // RP_CELLS a layer (only with rns)
     ct_check_result *res_dev = nullptr, *res_host = nullptr;
     uint32_t *sync_dev = nullptr;      // counters of the persistent launch (64 bytes)
     // stream of another lane that is idle while this one runs (null: none): the residue products of one group of

@@ -78,6 +78,7 @@ struct LayerDev {
     u128 *work;                 // caller workspace: A_0 + E | tA_p + Delta_p E for p < np (M x K each), then
                                 // the packed operands
     u128 *acc;                  // check accumulators, ACC_PER_LAYER entries (context scratch)
+    unsigned long long *uc;     // FO_RNS: RP_COPIES copies of the check sums of U (RP_CELLS cells), k_rns_open_right's
     u128 *Rf[MAXP], *tRf[MAXP], *Zf[MAXP], *tZf[MAXP];  // f > 0: truncated mask and output (M x N)
     int32_t f, in_bits;         // truncated fractional bits; dealer input width (0: uniform)
     int32_t cm;                 // CompactTag compresses along M (W^c = chi^T W) instead of N
@@ -169,8 +170,14 @@ constexpr int ACC_RP = 3 * ACC_W;
 constexpr int RP_CELLS = 1536;  // 64-bit cells (768 elements of 16 bytes)
 constexpr int RP_COPIES = RP_CELLS / 12;
 constexpr int NP_RP_COPIES = RP_CELLS / (4 * ACC_W);
-// k_rns_open_right adds its check sums of U into RP_COPIES more copies.
-constexpr int ACC_PER_LAYER = 3 * ACC_W + RP_CELLS;
+// The layers' accumulators lie this far apart, in a block of device memory of
+// their own (lane_init), with nothing else of a layer between them: thousands of
+// workgroups of k_check_batch and the passes add to the same few elements, and
+// how fast the memory takes that depends on where they lie.  k_check_batch of
+// 14 layers in SPDZ2k (SPDZ2K_CHECK in tests/test_accumulators.py) takes 620 us
+// so (178 of them without the additions); 785 with the accumulators behind the
+// lane's tables, 805 with twice the spacing, 840 with both.
+constexpr int ACC_PER_LAYER = 3 * ACC_W + RP_CELLS / 2;
 
 // cvec offsets (elements), see compacttag.h.  Compressing along M the same
 // offsets are taken with M replaced by N (cvec_off(N, K)), and the three

@@ -118,8 +118,8 @@ __global__ void k_np_zero(const LayerDev *__restrict__ Ls, int what) {
         const int64_t n = (1 + L.np) * L.K + (2 + 4 * L.np) * L.M;
         for (int64_t e = t0; e < n; e += stride) st(P<R>(L.cvec), e, Ring<R>::zero());
     }
-    if ((what & 2) && blockIdx.x == 0)  // 16-byte elements whatever the ring; the copies of the sums of U are two parties'
-        for (int i = threadIdx.x; i < ACC_PER_LAYER - RP_CELLS / 2; i += TPB) st(L.acc, i, u128{0, 0});
+    if ((what & 2) && blockIdx.x == 0)  // ACC_PER_LAYER 16-byte elements whatever the ring
+        for (int i = threadIdx.x; i < ACC_PER_LAYER; i += TPB) st(L.acc, i, u128{0, 0});
     if ((what & 4) && L.N <= 2) {
         const int64_t n = L.M * L.N;
         for (int64_t e = t0; e < n; e += stride)

@@ -22,9 +22,10 @@ __device__ __forceinline__ void zero_acc_body(const LayerDev *__restrict__ Ls, i
         const int64_t n = 3 * L.K + 10 * cvec_rows(L);
         for (int64_t e = t0; e < n; e += stride) st(P<R>(L.cvec), e, Ring<R>::zero());
     }
-    if ((what & 2) && g.x == 0) {  // ACC_PER_LAYER 16-byte elements whatever the ring, the last part only where it is used
-        const int n = L.fo == FO_RNS ? ACC_PER_LAYER : ACC_PER_LAYER - RP_CELLS / 2;
-        for (int i = threadIdx.x; i < n; i += TPB) st(L.acc, i, u128{0, 0});
+    if ((what & 2) && g.x == 0) {  // 16-byte elements whatever the ring
+        for (int i = threadIdx.x; i < ACC_PER_LAYER; i += TPB) st(L.acc, i, u128{0, 0});
+        if (L.fo == FO_RNS)
+            for (int i = threadIdx.x; i < RP_CELLS / 2; i += TPB) st(reinterpret_cast<u128 *>(L.uc), i, u128{0, 0});
     }
     if ((what & 4) && L.N <= SKINNY_MAX_N) {
         const int64_t n = L.M * L.N;
@@ -352,7 +353,7 @@ __device__ __forceinline__ void finalize_body(const LayerDev *__restrict__ Ls, i
     // and k_rns_open_right's copies of the U sums
     R u[3];
     if constexpr (sizeof(R) == 16) {
-        const unsigned long long *uc = u_cells(L);
+        const unsigned long long *uc = L.uc;
 #pragma unroll
         for (int i = 0; i < 3; i++) {
             u[i] = Ring<R>::zero();

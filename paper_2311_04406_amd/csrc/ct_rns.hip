@@ -355,7 +355,7 @@ __global__ __launch_bounds__(256, 2) void k_rns_open_right(const LayerDev *__res
             atomic_add128(L.cvec + (which == 0 ? o.Uc : which == 1 ? o.tBc0 : o.tBc1) + k, v);
         }
     }
-    if (check) wave_accumulate_limbs<3>(chk, u_cells(L) + 12 * ((wg * WAVES + wave) % RP_COPIES));
+    if (check) wave_accumulate_limbs<3>(chk, L.uc + 12 * ((wg * WAVES + wave) % RP_COPIES));
 }
 
 // Left operands: opens E = ([X]_0 - [A]_0) + ([X]_1 - [A]_1) and writes the

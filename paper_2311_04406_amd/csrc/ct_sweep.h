@@ -81,10 +81,6 @@ __device__ __forceinline__ unsigned long long *rp_cells(const LayerDev &L) {
     return reinterpret_cast<unsigned long long *>(P<R>(L.acc) + ACC_RP);
 }
 
-// The copies of the sums of U of a layer whose right operands k_rns_open_right
-// opens (Z_{2^128}), after the row pass's.
-__device__ __forceinline__ unsigned long long *u_cells(const LayerDev &L) { return rp_cells<u128>(L) + RP_CELLS; }
-
 // Adds each wavefront's NV sums (wave-reduced) into copy `copy` of the 4 NV
 // limb cells at `cells`, without a workgroup barrier or waiting for the
 // atomics: a wavefront that finishes early leaves at once.
