@@ -18,7 +18,9 @@
  *   - Every ct_u128 pointer in ct_layer_bufs is a DEVICE pointer, 16-byte
  *     aligned, allocated and owned by the caller; the library never frees
  *     caller memory and never allocates on the hot path (ct_tag_linear,
- *     ct_mac_check_device).  Buffers of different layers must not overlap.
+ *     ct_mac_check_device), but for the context's scratch of large products,
+ *     once, in the first call that uses it (ct_set_scratch takes it ahead or
+ *     declines it).  Buffers of different layers must not overlap.
  *   - Work is enqueued on the stream given in ct_params (NULL = the null
  *     stream) and is asynchronous unless stated otherwise.  A context is
  *     single-stream and not thread-safe; several contexts may coexist.
@@ -183,9 +185,7 @@ typedef struct {
  * [Delta]_p = draw(key_seed, stream (0xFFFF << 16) | (0x40 + p), 0) (F_MAC
  * Initialize, Appendix A) and keeps them resident, and allocates the
  * context's own fixed-size device scratch (descriptor tables, check
- * accumulators and, with k = s = 64, just under 2 GiB for the residues of
- * large products; a context that cannot have these forms every product by
- * digits).  *out receives the context; free it with ct_destroy. */
+ * accumulators).  *out receives the context; free it with ct_destroy. */
 ct_status ct_create(ct_ctx **out, const ct_params *params);
 
 /* Releases the context and its scratch after synchronizing its stream. */
@@ -258,12 +258,13 @@ ct_status ct_tag_linear_check(ct_ctx *ctx, ct_mode mode, const ct_layer_desc *L,
  * (CT_WORK_LEN_NP(M, K, N, parties) elements each, at 256-byte boundaries)
  * must fit in it together: otherwise CT_EINVAL with the sizes in
  * ct_last_error, and nothing runs.  Allocates no device memory (no hipMalloc,
- * hipFree or other allocating call); the caller still passes every input and
- * output buffer.  Every call on one GPU
- * uses the same array and leaves undefined contents in it (every byte a call
- * reads there it has written first), so calls that overlap on one GPU --
- * from contexts on different streams, or from several threads -- race and
- * must be serialized by the caller.  Asynchronous. */
+ * hipFree or other allocating call): large products go through residues only
+ * if an earlier call or ct_set_scratch allocated the context's scratch, else
+ * by digits.  The caller still passes every input and output buffer.  Every
+ * call on one GPU uses the same array and leaves undefined contents in it
+ * (every byte a call reads there it has written first), so calls that overlap
+ * on one GPU -- from contexts on different streams, or from several threads --
+ * race and must be serialized by the caller.  Asynchronous. */
 ct_status ct_tag_linear_check_static(ct_ctx *ctx, ct_mode mode, const ct_layer_desc *L, const ct_layer_bufs *B,
                                      int n, ct_check_result *out_dev);
 
@@ -286,6 +287,20 @@ ct_status ct_set_timing(ct_ctx *ctx, int enable);
  * default; ct_tag_linear the latter only) or the whole batch on the context stream (0: every kernel then runs alone,
  * as a per-kernel profile needs).  Results are the same either way. */
 ct_status ct_set_overlap(ct_ctx *ctx, int enable);
+
+/* Device memory for the residues of large products with k = s = 64 (see
+ * ct_product_paths): at most `bytes`, by default CT_SCRATCH_BYTES, allocated
+ * by the first call whose products use it (ct_tag_linear_check_static never
+ * allocates it) or, with now != 0, by this call; it stays in place until
+ * ct_destroy or the next ct_set_scratch.  0: none, every product by digits.  Less memory means
+ * more products one after the other, and what does not fit goes by digits; the
+ * results are the same.  Plans created afterwards allocate what their layers
+ * use, at most `bytes` each, and free it with the plan.  A context or plan
+ * that cannot have its scratch forms its products by digits from then on.
+ * Synchronizes and frees the scratch held before.  CT_ENOMEM: now != 0 and
+ * there is no memory. */
+#define CT_SCRATCH_BYTES ((2LL << 30) - (2LL << 20))
+ct_status ct_set_scratch(ct_ctx *ctx, int64_t bytes, int now);
 
 /* How ct_tag_linear_check (and ct_tag_linear_check_static, and plans created
  * afterwards) launch the online phase of a batch of two parties (Sec. 3.3:
@@ -394,6 +409,15 @@ ct_status ct_get_tuning(const ct_ctx *ctx, ct_mode mode, const ct_layer_desc *L,
  * ones. */
 ct_status ct_set_tuning(ct_ctx *ctx, const ct_tuning *t);
 
+/* How the online phase of these layers in one call would form their products,
+ * if the scratch it needs can be had: path[l] receives CT_PATH_ROW_PASS
+ * (N <= CT_SKINNY_N), CT_PATH_DIGITS or CT_PATH_RESIDUES.  Reads the
+ * descriptors' sizes only; CT_EINVAL for sizes that the calls refuse. */
+#define CT_PATH_ROW_PASS 0
+#define CT_PATH_DIGITS 1
+#define CT_PATH_RESIDUES 2
+ct_status ct_product_paths(const ct_ctx *ctx, ct_mode mode, const ct_layer_desc *L, int n, int32_t *path);
+
 /* ---- Captured plans: one graph launch per step (HIP graphs) ----
  *
  * A plan records the online phase of a fixed batch of layers (exactly as
@@ -405,8 +429,8 @@ ct_status ct_set_tuning(ct_ctx *ctx, const ct_tuning *t);
  * recomputes all outputs from the current contents of the input buffers.
  * A mixed batch is captured as two branches of the graph, as
  * ct_tag_linear_check runs it on two streams.  Creating a plan allocates
- * (its tables and what its products by residues need, below 2 GiB); launching
- * one does not. */
+ * (its tables and what its products by residues need, see ct_set_scratch);
+ * launching one does not. */
 typedef struct ct_plan ct_plan;
 
 /* Validates as ct_tag_linear_check does (out_dev may be NULL: no

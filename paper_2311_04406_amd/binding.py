@@ -91,6 +91,9 @@ class CtTuning(ctypes.Structure):
 
 # product kernel and workgroup tile shape (CT_TILE_*)
 TILE_AUTO, TILE_LDS_64x64, TILE_LDS_128x64, TILE_REGS_64x64, TILE_REGS_128x64, TILE_REGS_FIT = 0, 1, 2, 3, 4, 5
+# how a layer's products are formed (CT_PATH_*), and the default scratch of residue products (CT_SCRATCH_BYTES)
+PATH_ROW_PASS, PATH_DIGITS, PATH_RESIDUES = 0, 1, 2
+SCRATCH_BYTES = (2 << 30) - (2 << 20)
 # launch of the online phase (CT_LAUNCH_*)
 LAUNCH_STAGED, LAUNCH_PERSISTENT = 0, 1
 LAUNCH_WAIT_DEFAULT = 200000000  # 2 s of the device's 100 MHz wall clock
@@ -159,6 +162,8 @@ def load() -> ctypes.CDLL:
                                ctypes.POINTER(CtCheckResult)]
     L.ct_set_timing.argtypes = [vp, i]
     L.ct_set_overlap.argtypes = [vp, i]
+    L.ct_set_scratch.argtypes = [vp, ctypes.c_int64, i]
+    L.ct_product_paths.argtypes = [vp, i, ctypes.POINTER(CtLayerDesc), i, ctypes.POINTER(ctypes.c_int32)]
     L.ct_set_launch.argtypes = [vp, i]
     L.ct_set_launch_wait.argtypes = [vp, ctypes.c_uint64]
     L.ct_stage_times.argtypes = [vp, ctypes.POINTER(CtStageTime), i, ctypes.POINTER(ctypes.c_int)]
@@ -184,7 +189,7 @@ def load() -> ctypes.CDLL:
     L.ct_last_error.argtypes = [vp]
     L.ct_last_error.restype = ctypes.c_char_p
     for f in ("ct_create", "ct_destroy", "ct_key_shares", "ct_gen_triple_tags", "ct_tag_linear",
-              "ct_mac_check_device", "ct_mac_check", "ct_tag_linear_check_static", "ct_set_timing", "ct_set_overlap", "ct_set_launch", "ct_set_launch_wait", "ct_stage_times", "ct_tag_linear_check",
+              "ct_mac_check_device", "ct_mac_check", "ct_tag_linear_check_static", "ct_set_timing", "ct_set_overlap", "ct_set_scratch", "ct_product_paths", "ct_set_launch", "ct_set_launch_wait", "ct_stage_times", "ct_tag_linear_check",
               "ct_autotune", "ct_get_tuning", "ct_set_tuning", "ct_plan_create", "ct_plan_launch",
               "ct_plan_destroy", "ct_server_create", "ct_server_submit", "ct_server_poll", "ct_server_drain",
               "ct_server_layer", "ct_server_stats", "ct_server_destroy"):
@@ -416,6 +421,18 @@ class Context:
     def set_overlap(self, enable: bool):
         """Mixed batches on two streams (default) or all on the context stream."""
         self._check(self.lib.ct_set_overlap(self.h, int(enable)))
+
+    def set_scratch(self, nbytes: int = SCRATCH_BYTES, now: bool = False):
+        """Most device memory for the residues of large products (0: every
+        product by digits), allocated by the first call that uses it or at once."""
+        self._check(self.lib.ct_set_scratch(self.h, nbytes, int(now)))
+
+    def product_paths(self, mode: int, layers) -> list:
+        """PATH_* of each layer, as one call with these layers would form its products."""
+        n, D, _ = _arrays(layers)
+        out = (ctypes.c_int32 * n)()
+        self._check(self.lib.ct_product_paths(self.h, mode, D, n, out))
+        return list(out)
 
     def set_launch(self, mode: int):
         """LAUNCH_STAGED (one kernel per stage) or LAUNCH_PERSISTENT (one launch)."""

@@ -449,14 +449,14 @@ bool rns_alloc(RnsMemory &m) {
     return false;
 }
 
-// take[l]: layer l's online products go through residues.  A lane without
-// another to lend it a stream is the one beside the skinny layers'.
-std::vector<char> rns_layers(const ct_ctx *c, const Lane &ln, ct_mode mode, const ct_layer_desc *L, int n) {
+// take[l]: layer l's online products go through residues, if scratch of up to
+// cap bytes is there; *need receives what they use of it at most.  skinny: the
+// products run beside the pass of skinny layers that are not among the n.
+std::vector<char> rns_pick(const ct_ctx *c, ct_mode mode, const ct_layer_desc *L, int n, int64_t cap, bool skinny,
+                           int64_t *need) {
     std::vector<char> take(n, 0);
-    if (!rns_allowed(c) || !ln.rns || ln.rns->bytes <= 0) return take;
     std::vector<RnsShape> s;
     std::vector<int> at;
-    bool skinny = !ln.aux;
     for (int l = 0; l < n; l++)
         if (L[l].N > SKINNY_MAX_N) {
             s.push_back(rns_online_shape(L[l], c->np, mode == CT_MODE_COMPACT));
@@ -464,16 +464,34 @@ std::vector<char> rns_layers(const ct_ctx *c, const Lane &ln, ct_mode mode, cons
         } else {
             skinny = true;
         }
-    const std::vector<char> t = rns_choose(s, ln.rns->bytes, skinny);
-    int64_t need = 0;
+    const std::vector<char> t = rns_choose(s, cap, skinny);
+    *need = 0;
     for (size_t i = 0; i < at.size(); i++)
-        if (t[i]) need += rns_align(s[i].bytes(s[i].chunk_len(1)));
-    if (need > 0 && !ln.rns->scratch) {
-        ln.rns->bytes = std::min(ln.rns->bytes, need);
-        if (!rns_alloc(*ln.rns)) return take;
-    }
-    for (size_t i = 0; i < at.size(); i++) take[at[i]] = t[i];
+        if (t[i]) {
+            take[at[i]] = 1;
+            *need += rns_align(s[i].bytes(s[i].chunk_len(1)));
+        }
     return take;
+}
+
+// The layers of a call on lane ln that take the residue path, with its scratch
+// allocated: a context's by the first call that uses it (one that deals,
+// verifies, serves requests, runs plans or small layers holds none), all of it,
+// so that it then stays where it is.  A lane without another to lend it a
+// stream is the one beside the skinny layers'.
+std::vector<char> rns_layers(const ct_ctx *c, const Lane &ln, ct_mode mode, const ct_layer_desc *L, int n) {
+    const std::vector<char> none(n, 0);
+    if (!rns_allowed(c) || !ln.rns || ln.rns->bytes <= 0) return none;
+    RnsMemory &m = *ln.rns;
+    int64_t need = 0;
+    const std::vector<char> take = rns_pick(c, mode, L, n, m.bytes, !ln.aux, &need);
+    if (need == 0 || m.scratch) return take;
+    if (&m == &c->rns) {
+        if (c->no_alloc) return none;
+    } else {
+        m.bytes = std::min(m.bytes, need);  // a plan's: what its layers use
+    }
+    return rns_alloc(m) ? take : none;
 }
 
 // Assigns tile ranges to packing jobs; returns the total tile count.
@@ -781,7 +799,7 @@ ct_status ct_create(ct_ctx **out, const ct_params *p) {
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) == hipSuccess && cus > 0)
             c->num_cus = cus;
         const int ml = p->max_layers > 0 ? p->max_layers : 256;
-        if (c->eb == 16 && rns_alloc(c->rns)) c->main.rns = c->side.rns = &c->rns;
+        if (c->eb == 16) c->main.rns = c->side.rns = &c->rns;
         e = lane_init(c->main, reinterpret_cast<hipStream_t>(p->hip_stream), ml, c->np);
         hipStream_t side = nullptr;
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
@@ -1375,7 +1393,10 @@ ct_status ct_tag_linear_check_static(ct_ctx *c, ct_mode mode, const ct_layer_des
         b.work = reinterpret_cast<ct_u128 *>(static_cast<uint8_t *>(c->static_work) + off);
         off += bytes;
     }
-    return ct_tag_linear_check(c, mode, L, c->static_bufs.data(), n, out_dev);
+    c->no_alloc = true;
+    const ct_status s = ct_tag_linear_check(c, mode, L, c->static_bufs.data(), n, out_dev);
+    c->no_alloc = false;
+    return s;
 }
 
 ct_status ct_mac_check_device(ct_ctx *c, ct_mode mode, const ct_layer_desc *L, const ct_layer_bufs *B, int n,
@@ -1409,7 +1430,8 @@ ct_status ct_plan_create(ct_ctx *c, ct_mode mode, const ct_layer_desc *L, const 
     ct_plan *pl = new ct_plan();
     pl->ctx = c;
     hipStream_t st = nullptr, side = nullptr;
-    if (c->rns.scratch) pl->lane.rns = pl->side.rns = &pl->rns;
+    pl->rns.bytes = c->rns.bytes;
+    if (c->eb == 16) pl->lane.rns = pl->side.rns = &pl->rns;
     hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
     if (e == hipSuccess) e = lane_init(pl->lane, st, std::max(n, 1), c->np);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
@@ -1480,6 +1502,35 @@ ct_status ct_plan_destroy(ct_plan *pl) {
 ct_status ct_set_overlap(ct_ctx *c, int enable) {
     if (!c) return CT_EINVAL;
     c->overlap = enable != 0;
+    return CT_OK;
+}
+
+ct_status ct_set_scratch(ct_ctx *c, int64_t bytes, int now) {
+    if (!c) return CT_EINVAL;
+    if (bytes < 0) return fail(c, CT_EINVAL, "negative scratch size");
+    HIPCHK(c, hipSetDevice(c->device));
+    HIPCHK(c, hipStreamSynchronize(c->main.stream));
+    HIPCHK(c, hipStreamSynchronize(c->side.stream));
+    if (c->rns.scratch) HIPCHK(c, hipFree(c->rns.scratch));
+    c->rns.scratch = nullptr;
+    c->rns.bytes = bytes;
+    if (now && bytes > 0 && c->main.rns && !rns_alloc(c->rns)) return fail(c, CT_ENOMEM, "no memory for the scratch");
+    return CT_OK;
+}
+
+ct_status ct_product_paths(const ct_ctx *c, ct_mode mode, const ct_layer_desc *L, int n, int32_t *path) {
+    if (!c || !L || !path || n < 1 || n > c->main.max_layers || (mode != CT_MODE_SPDZ2K && mode != CT_MODE_COMPACT))
+        return CT_EINVAL;
+    for (int l = 0; l < n; l++) {  // sizes that the calls accept
+        const ct_layer_desc &d = L[l];
+        if (d.M < 1 || d.K < 1 || d.N < 1 || d.M >= (1LL << 31) || d.K >= (1LL << 31)) return CT_EINVAL;
+        if (d.N > SKINNY_MAX_N && (d.K >= (1LL << 21) || d.N >= (1LL << 22))) return CT_EINVAL;
+    }
+    int64_t need = 0;
+    std::vector<char> take(n, 0);
+    if (rns_allowed(c) && c->rns.bytes > 0) take = rns_pick(c, mode, L, n, c->rns.bytes, false, &need);
+    for (int l = 0; l < n; l++)
+        path[l] = L[l].N <= SKINNY_MAX_N ? CT_PATH_ROW_PASS : take[l] ? CT_PATH_RESIDUES : CT_PATH_DIGITS;
     return CT_OK;
 }
 

@@ -23,11 +23,11 @@ namespace ct {
 
 // Scratch of the residue products of a context or a plan: its lanes never use
 // it at once (the side lane runs between a fork from the main stream and the
-// join).  A context allocates it when it is created, a plan, if its layers take
-// that path, what they need of it.
+// join).  A context allocates it in the first call whose layers take that path
+// (or in ct_set_scratch), a plan at its creation what its layers need of it.
 struct RnsMemory {
-    uint8_t *scratch = nullptr;
-    int64_t bytes = RNS_SCRATCH_BYTES;  // 0: could not be had
+    uint8_t *scratch = nullptr;         // null: not allocated yet
+    int64_t bytes = RNS_SCRATCH_BYTES;  // of it, allocated or to be; 0: none, every product by digits
 };
 
 struct Lane {
@@ -88,6 +88,7 @@ struct ct_ctx {
     int launch_mode = CT_LAUNCH_STAGED;  // ct_set_launch
     uint64_t launch_wait = CT_LAUNCH_WAIT_DEFAULT;  // ct_set_launch_wait
     ct::RnsMemory rns;  // of both lanes
+    bool no_alloc = false;  // inside ct_tag_linear_check_static
     std::string err;
     // per-launch timing: event pairs recorded around each kernel of the main lane
     bool timing = false;

@@ -11,11 +11,11 @@
 
 namespace ct {
 
-// Most scratch for residue planes and residues.  A call whose layers need more
+// Most scratch for residue planes and residues by default.  A call whose layers need more
 // runs them in groups, one after the other: twelve encoders took 7.9 ms in
 // groups of half a GiB, 7.5 ms of one GiB and of sixteen.  Just below 2 GiB,
 // where hipMalloc takes 70 us (330 us from 2 GiB on).
-constexpr int64_t RNS_SCRATCH_BYTES = (2LL << 30) - (2LL << 20);
+constexpr int64_t RNS_SCRATCH_BYTES = CT_SCRATCH_BYTES;
 constexpr int RNS_MAX_CHUNKS = 64;
 
 // What the cost of a layer's products depends on: nl left and nr right
