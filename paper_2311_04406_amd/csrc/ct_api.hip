@@ -421,25 +421,6 @@ PackJob make_job(const u128 *src, u128 *dst, int64_t rows, int64_t cols, int sid
 bool rns_allowed(const ct_ctx *c) {
     return c->eb == 16 && c->fallback.tile == CT_TILE_AUTO && c->launch_mode == CT_LAUNCH_STAGED;
 }
-// The products of the online phase of a layer with n parties: E [B]_p +
-// ([A]_p or A_0 + E) U, in SPDZ2k also E [tB]_p + ([tA]_p + [Delta]_p E) U.
-RnsShape rns_online_shape(const ct_layer_desc &d, int np, bool compact) {
-    RnsShape s;
-    s.M = d.M; s.K = d.K; s.N = d.N;
-    s.nl = s.nr = compact ? np + 1 : 2 * np + 1;
-    s.outs = compact ? np : 2 * np;
-    if (np > 2 && compact) s.rate = 0.85e5;  // an encoder of three parties: 1314 us by digits, 1340 by residues
-    if (np == 2 && compact) {
-        const bool cm = CT_COMPRESS_ALONG_M(d.M, d.N, d.compress);
-        // one pass opens, compresses and converts, but along M only the digit path's (595 us for a drawn batch of
-        // such layers by digits, 650 by residues where 1.0e5 sent them there)
-        if (d.conv_c == 0) s.rate = cm ? 0.76e5 : 1.38e5;
-        // only layers compressed along M open U apart from its conversion here and together with it there
-        if (d.conv_c == 0 && cm) s.refetch = 48.0 * d.K * d.N;
-    }
-    return s;
-}
-
 // Scratch of m.bytes; without it (m.bytes = 0) every product runs by digits.
 bool rns_alloc(RnsMemory &m) {
     if (hipMalloc(&m.scratch, m.bytes) == hipSuccess) return true;

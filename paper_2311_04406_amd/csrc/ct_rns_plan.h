@@ -33,8 +33,8 @@ struct RnsShape {
     // fewest chunks of K whose planes fit beside the residues in cap bytes; 0: none
     int chunks(int64_t cap) const {
         if (segs * K > RNS_MAX_TERMS) return 0;
-        for (int c = 1; c <= RNS_MAX_CHUNKS && (c - 1) * chunk_len(c) < K; c++)
-            if (bytes(chunk_len(c)) <= cap) return c;
+        for (int c = 1; c <= RNS_MAX_CHUNKS; c++)  // some c leave their last chunks empty: the length is rounded up
+            if ((c - 1) * chunk_len(c) < K && bytes(chunk_len(c)) <= cap) return c;
         return 0;
     }
     double macs() const { return (double)outs * segs * M * K * N; }
@@ -53,6 +53,25 @@ struct RnsShape {
                outs * pm * pn / 5.3e4;
     }
 };
+
+// The products of the online phase of a layer with n parties: E [B]_p +
+// ([A]_p or A_0 + E) U, in SPDZ2k also E [tB]_p + ([tA]_p + [Delta]_p E) U.
+inline RnsShape rns_online_shape(const ct_layer_desc &d, int np, bool compact) {
+    RnsShape s;
+    s.M = d.M; s.K = d.K; s.N = d.N;
+    s.nl = s.nr = compact ? np + 1 : 2 * np + 1;
+    s.outs = compact ? np : 2 * np;
+    if (np > 2 && compact) s.rate = 0.85e5;  // an encoder of three parties: 1314 us by digits, 1340 by residues
+    if (np == 2 && compact) {
+        const bool cm = CT_COMPRESS_ALONG_M(d.M, d.N, d.compress);
+        // one pass opens, compresses and converts, but along M only the digit path's (595 us for a drawn batch of
+        // such layers by digits, 650 by residues where 1.0e5 sent them there)
+        if (d.conv_c == 0) s.rate = cm ? 0.76e5 : 1.38e5;
+        // only layers compressed along M open U apart from its conversion here and together with it there
+        if (d.conv_c == 0 && cm) s.refetch = 48.0 * d.K * d.N;
+    }
+    return s;
+}
 
 // Which of the layers of a call (those with N > SKINNY_MAX_N) take the residue
 // path.  Each path brings launches of its own, tens of microseconds on a small
