@@ -356,7 +356,10 @@ ct_status ct_stage_times(ct_ctx *ctx, ct_stage_time *out, int max, int *count);
  * wavefront, which only the k = s = 32 set has registers for (with
  * k = s = 64 the 128 x 64 shapes run as 64 x 64).
  *   CT_TILE_AUTO: register-streamed; 128 x 64 for k = s = 32 when the launch
- *     has at least two such tiles per compute unit, else 64 x 64.
+ *     has at least two such tiles per compute unit, else 64 x 64; a staged
+ *     launch of less than one 64 x 64 tile per compute unit (k = s = 32: half
+ *     a tile) and split_target 0 may have the wavefronts of a workgroup share
+ *     the K slices of one 32 x 32 tile.
  *   CT_TILE_LDS_*: operand digit tiles copied global -> LDS, one K slice
  *     ahead, fragments read from LDS (a workgroup barrier per K slice).
  *   CT_TILE_REGS_*: every wavefront loads its digit fragments from global
@@ -395,7 +398,11 @@ typedef struct {
  * CT_TILE_REGS_FIT, and for k = s = 32 also the 128 x 64 shapes), then
  * split_target in 0, 16, 32, 64, 128, xcd_remap in 0, 1, 4, 8, 16 and
  * group_m in 1, 2, 4, 8, 16, 64, each under the best so far, then the tile
- * shape again.  Later calls of the same class use the choice.  Synchronizes;
+ * shape again.  Under CT_TILE_AUTO and split_target 0 the last candidate is
+ * what CT_TILE_AUTO does with a launch of few tiles (the wavefronts of a
+ * workgroup share the K slices of one tile); if it is the fastest, such staged
+ * launches of the class take it and the others the choice reported.  Later
+ * calls of the same class use the choice.  Synchronizes;
  * allocates the timing event pool if timing was never enabled; the stage
  * times of ct_stage_times are left as they were.  best (may be NULL)
  * receives the choice. */

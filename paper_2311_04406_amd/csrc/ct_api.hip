@@ -567,15 +567,17 @@ int64_t gemm_length(const std::vector<GemmProb> &probs, int num_cus, int wg, int
 // Whether the wavefronts of a workgroup share the K slices of one output tile
 // (WS_K4), and into how many slices per workgroup K is then split: for launches
 // of fewer than one 64 x 64 tile per compute unit (k = s = 32, with a quarter
-// of the products per fragment: half a tile) whose configuration is left to the library, if it is the shorter way by gemm_length.  Larger launches
-// keep every compute unit busy without, and read half as many fragments.
+// of the products per fragment: half a tile) whose configuration is left to the
+// library, or was found slower by ct_autotune, if it is the shorter way by
+// gemm_length.  Larger launches keep every compute unit busy without, and read
+// half as many fragments.
 // Measured with the launch for constant terms, us before and after:
 // 64 x 128 x 32 27.6 and 15.7, 256 x 256 x 256 39.8 and 26.0, 96 x 1024 x 1024
 // 93.7 and 57.7, 130 x 4608 x 300 131.7 and 109.9; the other way round for
 // 512 x 64 x 512 (24.7 and 32.5), which the rule leaves as it was, and for two
 // batches of 272 and 396 tiles with short K (72 and 84, 60 and 88).
 int64_t k4_target(const std::vector<GemmProb> &probs, int num_cus, const GemmTuning &tu, int eb) {
-    if (tu.tile != CT_TILE_AUTO || tu.split_target != 0) return 0;
+    if (!tu.shared && (tu.tile != CT_TILE_AUTO || tu.split_target != 0)) return 0;
     int64_t tiles = 0, steps = 0, most = 0;
     for (const auto &p : probs) {
         const int64_t t = (int64_t)((p.M + 63) / 64) * ((p.N + 63) / 64), n = (int64_t)((p.K + 31) / 32) * (p.Lp2 ? 2 : 1);
@@ -614,7 +616,7 @@ int plan_gemms(std::vector<GemmProb> &probs, int num_cus, const GemmTuning &tu, 
         total_steps += (int64_t)p.tiles_m * p.tiles_n * p.nsteps;
     }
     int64_t target = k4 ? k4 : default_target(total_steps, num_cus);
-    if (tu.split_target > 0) target = std::min<int64_t>(std::max<int64_t>(tu.split_target, 8), MAX_STEPS_PER_SPLIT);
+    if (!k4 && tu.split_target > 0) target = std::min<int64_t>(std::max<int64_t>(tu.split_target, 8), MAX_STEPS_PER_SPLIT);
     int tile = 0;
     *any_accum = false;
     for (size_t i = 0; i < probs.size();) {
@@ -1627,6 +1629,13 @@ ct_status ct_autotune(ct_ctx *c, ct_mode mode, const ct_layer_desc *L, const ct_
             if (s == CT_OK && xcd != best.xcd_remap) { GemmTuning t = best; t.xcd_remap = xcd; s = trial(t); }
         for (int g : groups)
             if (s == CT_OK && g != best.group_m) { GemmTuning t = best; t.group_m = g; s = trial(t); }
+    }
+    // an untuned call of few tiles has its wavefronts share K slices: the last candidate, beside the tile shape
+    // found for the class's other launches (the persistent one, and batches of more tiles)
+    if (s == CT_OK && c->fallback.tile == CT_TILE_AUTO && c->fallback.split_target == 0) {
+        GemmTuning t = best;
+        t.shared = 1;
+        s = trial(t);
     }
     std::copy(saved_ms, saved_ms + ST_COUNT, c->stage_ms);
     std::copy(saved_n, saved_n + ST_COUNT, c->stage_n);

@@ -364,6 +364,7 @@ struct GemmTuning {
     int32_t xcd_remap;     // 0: identity; 1: contiguous range per XCD; G >= 2: groups of G tiles per XCD
     int32_t split_target;  // K slices per tile; 0 = enough tiles for two rounds over the CUs
     int32_t tile;          // CT_TILE_*: kernel and workgroup tile (0 = by the launch's size)
+    int32_t shared = 0;    // 1: tuned launches may have their wavefronts share K slices (WS_K4), as untuned ones may
 };
 
 // Unpacked product for the dealer's layers with N <= SKINNY_MAX_N:
