@@ -167,6 +167,40 @@ def stage_work(stage: str, specs, mode: str, f: int = 0, kbits: int = 64, compre
 
 RNS_STAGES = ("rns_open", "rns_pack", "rns_gemm", "rns_fold")
 
+def batch_work(stage: str, specs, residues, mode: str, **kw):
+    """stage_work over a batch whose layers take different product paths:
+    residues[l] says whether layer l's products go through residues."""
+    by = [s for s, r in zip(specs, residues) if r]
+    rest = [s for s, r in zip(specs, residues) if not r]
+    parts = []
+    if by and stage != "ring_gemm":
+        parts.append(stage_work(stage, by, mode, rns=True, **kw))
+    if rest and stage not in RNS_STAGES:
+        parts.append(stage_work(stage, rest, mode, **kw))
+    parts = [p for p in parts if p is not None]
+    return (parts[0][0], sum(p[1] for p in parts)) if parts else None
+
+
+def stage_figures(stages, work, steps: int, ms: float):
+    """Per stage of `steps` steps of ms milliseconds: time per launch, share of
+    the step and, where work(stage) is known, the rate over the step's launches
+    together (a stage may have several)."""
+    rows = {}
+    for name, (tot_ms, n) in stages.items():
+        row = {"ms_per_launch": round(tot_ms / max(n, 1), 5), "launches": n, "share_of_step": round(tot_ms / steps / ms, 4)}
+        w, per_step = work(name), tot_ms / steps * 1e-3
+        if w is not None and w[1] > 0 and per_step > 0:
+            bound, units = w
+            if bound == "hbm":
+                row.update(bound="hbm", achieved_GBps=round(units / per_step / 1e9, 1),
+                           frac=round(units / per_step / 1e9 / HBM_PEAK_GBS, 4), algorithmic_bytes=units)
+            else:
+                row.update(bound="mfma", achieved_TOPS=round(units / per_step / 1e12, 1),
+                           frac=round(units / per_step / 1e12 / INT8_PEAK_TOPS, 4), int8_ops=units)
+        rows[name] = row
+    return rows
+
+
 # Sources that determine what the device kernels do; the hardware counters in
 # profiles/traffic.json are valid only for the digest they were taken on.
 KERNEL_SOURCES = ("ct_device.h", "ct_internal.h", "ct_sweep.h", "ct_passes.h", "ct_kernels.hip", "ct_gemm.hip",
@@ -487,7 +521,7 @@ def main():
 
     import torch
     from paper_2311_04406_amd import MODE_COMPACT, MODE_SPDZ2K, RESULT_WORDS, Context, Layer, workloads
-    from paper_2311_04406_amd.binding import LAUNCH_PERSISTENT, LAUNCH_STAGED
+    from paper_2311_04406_amd.binding import LAUNCH_PERSISTENT, LAUNCH_STAGED, PATH_RESIDUES
 
     if args.config == "serving":
         return serving_main(args, torch)
@@ -538,26 +572,10 @@ def main():
     value = mkn * args.steps / T / 1e9
 
     # per-stage figures and the dominant kernel's roofline
-    stage_rows = {}
-    rns = "rns_gemm" in stages
-    for name, (tot_ms, n) in stages.items():
-        if name in RNS_STAGES:
-            n = args.steps  # the launches of a step's groups taken together
-        avg = tot_ms / max(n, 1)
-        w = stage_work(name, specs, args.mode, args.f, args.kbits, args.compress, implicit, args.parties, rns)
-        # a batch on both product paths: which layers are on which is not known here
-        if rns and "ring_gemm" in stages and name in ("open_u", "open_pack", "pack", "row_pass", "ring_gemm") + RNS_STAGES:
-            w = None
-        row = {"ms_per_launch": round(avg, 5), "launches": n, "share_of_step": round(tot_ms / args.steps / ms, 4)}
-        if w is not None and w[1] > 0:
-            bound, units = w
-            if bound == "hbm":
-                row.update(bound="hbm", achieved_GBps=round(units / (avg * 1e-3) / 1e9, 1),
-                           frac=round(units / (avg * 1e-3) / 1e9 / HBM_PEAK_GBS, 4), algorithmic_bytes=units)
-            else:
-                row.update(bound="mfma", achieved_TOPS=round(units / (avg * 1e-3) / 1e12, 1),
-                           frac=round(units / (avg * 1e-3) / 1e12 / INT8_PEAK_TOPS, 4), int8_ops=units)
-        stage_rows[name] = row
+    residues = [p == PATH_RESIDUES for p in ctx.product_paths(mode_id, layers)]
+    stage_rows = stage_figures(stages, lambda name: batch_work(name, specs, residues, args.mode, f=args.f, kbits=args.kbits,
+                                                               compress=args.compress, implicit=implicit,
+                                                               parties=args.parties), args.steps, ms)
     ranked = sorted(((k, v) for k, v in stage_rows.items() if "bound" in v),
                     key=lambda kv: -kv[1]["ms_per_launch"] * kv[1]["launches"])
     roofline = None
