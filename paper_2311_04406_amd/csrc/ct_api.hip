@@ -338,9 +338,8 @@ ct_status stage_layers(ct_ctx *c, Lane &ln, const ct_layer_desc *L, const ct_lay
     return CT_OK;
 }
 
-// One copy, up to the end of the last table in use: on the device it is a
-// kernel of 3 to 5 us whatever its size (6 KB a layer), and the small layers'
-// calls had three of them.
+// The tables up to the end of the last one in use, in copies of upload_piece
+// bytes: the small layers' calls need one of them.
 ct_status upload(ct_ctx *c, Lane &ln, int n, int nprobs, int njobs = 0, int nskinny = 0,
                  const RnsPlan &rns = RnsPlan()) {
     const uint8_t *end = reinterpret_cast<const uint8_t *>(ln.layers_host + n);
@@ -353,7 +352,9 @@ ct_status upload(ct_ctx *c, Lane &ln, int n, int nprobs, int njobs = 0, int nski
     upto(ln.rns_open_host + rns.nopen, rns.nopen);
     upto(ln.rns_probs_host + rns.nprobs, rns.nprobs);
     upto(ln.rns_jobs_host + rns.njobs, rns.njobs);
-    HIPCHK(c, hipMemcpyAsync(ln.dev, ln.host, end - ln.host, hipMemcpyHostToDevice, ln.stream));
+    const int64_t bytes = end - ln.host, piece = upload_piece(bytes);
+    for (int64_t at = 0; at < bytes; at += piece)
+        HIPCHK(c, hipMemcpyAsync(ln.dev + at, ln.host + at, std::min(piece, bytes - at), hipMemcpyHostToDevice, ln.stream));
     HIPCHK(c, hipEventRecord(ln.upload_done, ln.stream));
     return CT_OK;
 }

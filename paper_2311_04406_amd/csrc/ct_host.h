@@ -58,6 +58,14 @@ struct Lane {
     bool timed = false;                // per-launch event timing (the context's own lane only)
 };
 
+// Bytes per copy of a table upload (about 2 KB a layer and more).  A copy of up
+// to 16 KB from pinned memory takes 2.5 us of the device's time, a larger one
+// 17 (measured between two kernels: 148.2 us with 16 KB in between, 162.2 with
+// 16.25 KB, 150.6 with 2 x 16 KB, 155.2 with 4 x 16 KB, 163.0 with 64 KB), and
+// every copy 6 us of the host's, so tables of up to four pieces go up in pieces.
+constexpr int64_t UPLOAD_PIECE = 16 << 10;
+inline int64_t upload_piece(int64_t bytes) { return bytes <= 4 * UPLOAD_PIECE ? UPLOAD_PIECE : bytes; }
+
 // Allocates the lane's tables for up to max_layers layers of np parties (the
 // stream is the caller's).  On failure the lane is left for lane_free.
 hipError_t lane_init(Lane &ln, hipStream_t stream, int max_layers, int np);
