@@ -257,7 +257,7 @@ void fill_layer(const ct_ctx *c, u128 *acc, const ct_layer_desc &d, const ct_lay
 }
 
 struct Sizes {
-    int64_t mk = 0, kn = 0, mn = 0, m = 0, k = 0, cvec = 0, kn_items = 0, mn_items = 0, row_items = 0,
+    int64_t mk = 0, kn = 0, mn = 0, m = 0, k = 0, cvec = 0, kn_items = 0, mn_items = 0, mn_row_items = 0, mn_col_items = 0, row_items = 0,
             skinny_mn = 0, col_tag = 0, nr = 0, conv_items = 0;
     bool skinny = false, cm = false, conv_n = false;
 };
@@ -275,6 +275,7 @@ Sizes max_sizes(const ct_layer_desc *L, int n) {
         // a convolution's U is opened elementwise on its input (about 4 elements per lane)
         s.kn_items = std::max(s.kn_items, d.conv_c > 0 ? (int64_t)CT_RIGHT_LEN(d) / 256 + 1 : sweep_items(d.K, d.N));
         s.mn_items = std::max(s.mn_items, sweep_items(d.M, d.N));
+        if (!CT_COMPRESS_ALONG_M(d.M, d.N, d.compress)) s.mn_row_items = std::max(s.mn_row_items, sweep_items(d.M, d.N));
         s.row_items = std::max(s.row_items, row_items(d.M, d.K));
         s.nr = std::max(s.nr, (int64_t)CT_RIGHT_LEN(d));
         if (d.conv_c > 0 && !CT_COMPRESS_ALONG_M(d.M, d.N, d.compress)) {
@@ -286,7 +287,7 @@ Sizes max_sizes(const ct_layer_desc *L, int n) {
             // column-strip row pass, column sweeps of the M x N pass and of the compact products
             s.cm = true;
             s.row_items = std::max(s.row_items, (cm_share(d.M, d.K, d.N) ? COL_WAVES : 1) * cm_items(d.M, d.K, d.N));
-            s.mn_items = std::max(s.mn_items, COL_WAVES * col_sweep_items(d.M, d.N));
+            s.mn_col_items = std::max(s.mn_col_items, COL_WAVES * col_sweep_items(d.M, d.N));
             s.col_tag = std::max(s.col_tag, col_sweep_items(d.K, d.N));
         }
         if (d.N <= SKINNY_MAX_N) {
@@ -1161,7 +1162,8 @@ ct_status prepare_online(ct_ctx *c, Lane &ln, ct_mode mode, const ct_layer_desc 
     P.max_kn_items = sz.kn_items;
     P.max_row_items = sz.row_items;
     P.max_mn = sz.mn;
-    P.max_mn_items = sz.mn_items;
+    P.max_mn_items = compact ? sz.mn_row_items : sz.mn_items;
+    P.max_mn_col_items = sz.mn_col_items;
     P.any_cm = P.all_cm = compact && sz.cm;
     for (int l = 0; l < n; l++) P.all_cm &= ln.layers_host[l].cm != 0;
     P.max_col_tag = sz.col_tag;
@@ -1245,7 +1247,8 @@ ct_status enqueue_online(ct_ctx *c, Lane &ln, const OnlineLaunch &P) {
     ct_status s = products();
     const ct_status j = join_products(c, ln, over);  // also on failure, so that the streams stay joined
     if (s != CT_OK || (s = j) != CT_OK) return s;
-    LAUNCH(c, ln, ST_POST, launch_post(c->eb, ln.layers_dev, n, P.flags, P.max_mn_items, P.any_cm, P.all_cm, ln.stream));
+    LAUNCH(c, ln, ST_POST, launch_post(c->eb, ln.layers_dev, n, P.flags, P.max_mn_items, P.any_cm ? P.max_mn_col_items : 0, P.all_cm,
+                                    ln.stream));
     if (P.compact) LAUNCH(c, ln, ST_COMPACT_FINAL, launch_compact_final(c->eb, ln.layers_dev, n, P.flags, ln.stream));
     if (P.check) LAUNCH(c, ln, ST_FINALIZE, launch_finalize(c->eb, ln.layers_dev, n, P.out_dev, ln.stream));
     return CT_OK;

@@ -140,7 +140,7 @@ struct OnlineLaunch {
     ct_mode mode = CT_MODE_COMPACT;
     GemmTuning tu;
     RnsPlan rns;
-    int64_t max_zero = 0, max_kn_items = 0, max_row_items = 0, max_mn = 0, max_mn_items = 0, max_col_tag = 0,
+    int64_t max_zero = 0, max_kn_items = 0, max_row_items = 0, max_mn = 0, max_mn_items = 0, max_mn_col_items = 0, max_col_tag = 0,
             max_conv_items = 0;
     // n-party path
     int64_t max_open = 0, max_skinny_items = 0, max_compress_items = 0, max_gemv_items = 0, max_cvec_np = 0;

@@ -412,8 +412,12 @@ hipError_t launch_open_pack(int eb, const LayerDev *L, int n, int flags, int max
 // variants: bit v (bit VARIANT_CM + v) set if some layer takes row-pass variant v (0, 1, 2, 4, 8)
 // (of the pass of layers compressed along M)
 hipError_t launch_row_pass(int eb, const LayerDev *L, int n, int flags, int64_t max_items, int variants, hipStream_t st);
-// any_cm, all_cm: layers compressed along M (they take a kernel of their own)
-hipError_t launch_post(int eb, const LayerDev *L, int n, int flags, int64_t max_items, bool any_cm, bool all_cm,
+// Layers compressed along M take a kernel of their own, with a grid of its own:
+// max_items of the other layers, max_col_items of these (0: there are none;
+// all_cm: there are no others).  Every workgroup of a layer that is not the
+// kernel's leaves at once, but is launched: the pass over 27 layers (k = s = 32)
+// took 387 us with the larger of the two grids for both kernels, 369 so.
+hipError_t launch_post(int eb, const LayerDev *L, int n, int flags, int64_t max_items, int64_t max_col_items, bool all_cm,
                        hipStream_t st);
 hipError_t launch_compact_final(int eb, const LayerDev *L, int n, int flags, hipStream_t st);
 hipError_t launch_col_tag(int eb, const LayerDev *L, int n, int64_t max_items, hipStream_t st);

@@ -514,11 +514,10 @@ __global__ __launch_bounds__(TPB) void k_post_cm(const LayerDev *__restrict__ Ls
     post_body<R, true>(Ls, flags, hw_grid());
 }
 
-hipError_t launch_post(int eb, const LayerDev *L, int n, int flags, int64_t max_items, bool any_cm, bool all_cm,
+hipError_t launch_post(int eb, const LayerDev *L, int n, int flags, int64_t max_items, int64_t max_col_items, bool all_cm,
                        hipStream_t st) {
-    const dim3 g(grid_items(max_items), n);
-    if (!all_cm) LAUNCH_RING(eb, k_post, g, dim3(TPB), st, L, flags);
-    if (any_cm) LAUNCH_RING(eb, k_post_cm, g, dim3(TPB), st, L, flags);
+    if (!all_cm) LAUNCH_RING(eb, k_post, dim3(grid_items(max_items), n), dim3(TPB), st, L, flags);
+    if (max_col_items > 0) LAUNCH_RING(eb, k_post_cm, dim3(grid_items(max_col_items), n), dim3(TPB), st, L, flags);
     return hipGetLastError();
 }
 
