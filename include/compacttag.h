@@ -284,8 +284,9 @@ ct_status ct_set_timing(ct_ctx *ctx, int enable);
 /* Whether ct_tag_linear_check and plans created afterwards run the two
  * layer groups of a mixed batch, and the residue products of one group of
  * layers and the openings of the next, on two streams (enable != 0, the
- * default; ct_tag_linear the latter only) or the whole batch on the context stream (0: every kernel then runs alone,
- * as a per-kernel profile needs).  Results are the same either way. */
+ * default; ct_tag_linear the latter only) or the whole batch on the context
+ * stream (0: every kernel then runs alone, as a per-kernel profile needs).
+ * Results are the same either way. */
 ct_status ct_set_overlap(ct_ctx *ctx, int enable);
 
 /* Device memory for the residues of large products with k = s = 64 (see

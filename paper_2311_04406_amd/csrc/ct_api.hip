@@ -2,10 +2,11 @@
 //
 // A call validates its layers, writes one LayerDev record per layer (sizes,
 // key shares, generator stream keys, buffer pointers) and the GEMM problem
-// list into pinned staging memory, uploads them with one asynchronous copy on
+// list into pinned staging memory, uploads them with asynchronous copies on
 // the context stream, and enqueues the kernels of the requested phase.  The
 // staging area is reused only after the previous upload has completed (an
-// event), so a call never allocates.
+// event), so a call allocates nothing but, once in a context's life, the
+// scratch of the residue products (rns_layers).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

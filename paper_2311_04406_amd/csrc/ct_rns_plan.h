@@ -11,10 +11,10 @@
 
 namespace ct {
 
-// Most scratch for residue planes and residues by default.  A call whose layers need more
-// runs them in groups, one after the other: twelve encoders took 7.9 ms in
-// groups of half a GiB, 7.5 ms of one GiB and of sixteen.  Just below 2 GiB,
-// where hipMalloc takes 70 us (330 us from 2 GiB on).
+// Most scratch for residue planes and residues by default.  A call whose layers
+// need more runs them in groups, one after the other: twelve encoders took 7.9
+// ms in groups of half a GiB, 7.5 ms of one GiB and of sixteen.  Just below 2
+// GiB, where hipMalloc takes 70 us (330 us from 2 GiB on).
 constexpr int64_t RNS_SCRATCH_BYTES = CT_SCRATCH_BYTES;
 constexpr int RNS_MAX_CHUNKS = 64;
 
@@ -46,7 +46,9 @@ struct RnsShape {
     // parties, both protocols) and 60 batches timed on either path.  With two
     // parties and CompactTag a layer of 2048^3 takes 2061 us by residues and 3661
     // by digits, 256 x 768 x 768 201 and 211, 64 x 4096 x 4096 1438 and 1224; an
-    // encoder in SPDZ2k 1152 and 1191.  The sign changes near M N / (M + N) = 80.
+    // encoder in SPDZ2k 1152 and 1191, which rns_choose leaves with digits (the
+    // estimate, 76 of 821 us of digit products, is below its tenth).  The sign
+    // changes near M N / (M + N) = 80.
     double saves_us() const {
         const double pm = 32.0 * rns_blocks(M), pn = 32.0 * rns_blocks(N);
         return digits_us() - (double)outs * segs * pm * K * pn * (36 / 0.9e9) - (nl * pm + nr * pn) * K / rate - refetch / 5.5e6 -
